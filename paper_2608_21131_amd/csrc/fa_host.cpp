@@ -370,6 +370,8 @@ void fa_ctx_destroy(fa_ctx* c) {
   (void)hipFree(c->d_twt_inv);
   (void)hipFree(c->d_twr_fwd);
   (void)hipFree(c->d_twr_inv);
+  (void)hipFree(c->d_tws_fwd);
+  (void)hipFree(c->d_tws_inv);
   (void)hipFree(c->d_mu_hat);
   (void)hipFree(c->d_md_hat);
   (void)hipFree(c->d_mu_scale);
@@ -507,7 +509,9 @@ static int ctx_build(const fa_params* prm, const std::vector<u64>& primes, fa_ct
       (rc = dev_alloc(&c->d_twr_inv, twr_i.size())) || (rc = dev_alloc(&c->d_mu_hat, mu_hat.size())) ||
       (rc = dev_alloc(&c->d_md_hat, md_hat.size())) || (rc = dev_alloc(&c->d_mu_scale, (size_t)L)) ||
       (rc = dev_alloc(&c->d_md_scale, (size_t)K)) ||
-      (rc = dev_alloc(&c->d_s, (size_t)np * n))) {
+      (rc = dev_alloc(&c->d_s, (size_t)np * n)) ||
+      (fa::small_ring(c) &&
+       ((rc = dev_alloc(&c->d_tws_fwd, (size_t)np * n)) || (rc = dev_alloc(&c->d_tws_inv, (size_t)np * n))))) {
     fa_ctx_destroy(c);
     return rc;
   }
@@ -527,6 +531,10 @@ static int ctx_build(const fa_params* prm, const std::vector<u64>& primes, fa_ct
   up(c->d_mu_scale, c->h_mu_scale);
   up(c->d_md_scale, c->h_md_scale);
   if (e == hipSuccess) e = hipMemset(c->d_s, 0, (size_t)np * n * 8);
+  if (e == hipSuccess && fa::small_ring(c)) {
+    fa::sr_tables(c, 0);
+    if ((e = hipGetLastError()) == hipSuccess) e = hipStreamSynchronize(0);
+  }
   if (e != hipSuccess) {
     fa_ctx_destroy(c);
     return fail(FA_E_HIP, "fa_ctx_create: %s", hipGetErrorString(e));
@@ -1343,10 +1351,12 @@ size_t score_ws(const fa_ctx* c, int nb, int d, int B) {
 // Extended digits (NTT form) of the c1 of `batch` ciphertexts cts + b * ct_stride.
 // y (per item [L][N]) receives c1 after the row pass of its inverse transform
 // (scratch); ext receives every converted limb (pass_b false: the first
-// forward pass only).  The ciphertexts are only read.
+// forward pass only).  The ciphertexts are only read.  Small rings leave y
+// alone and need ext_stride = dnum np N.
 static void modup(fa_ctx* c, const double* cts, size_t ct_stride, int batch, double* y, size_t y_stride,
                   double* ext, size_t ext_stride, hipStream_t s, bool pass_b = true) {
   const size_t n = c->n, L = c->L;
+  if (fa::small_ring(c)) return fa::sr_modup(c, cts + L * n, ct_stride, batch, 0, 1, ext, s);
   {
     // the row pass of the inverse transform; the fused ModUp kernel finishes it
     fa::LimbBatch inv(c, s, false, true);
@@ -1388,10 +1398,19 @@ static void moddown_polys(fa_ctx* c, double* u, int count, double* conv, const d
 // Key switch and ModDown of `count` rotations: outs[j] = (c0s[j][pi] + ModDown(u_0),
 // ModDown(u_1)) with u = sum_i sigma(ext_i) key_i.  The special-prime part of u
 // goes through u (per rotation [2][np][N]); the ciphertext-prime part is formed
-// inside the finishing kernel.  conv: per rotation [2][L][N] scratch.
+// inside the finishing kernel.  conv: per rotation [2][L][N] scratch.  b0s / b1s
+// (or null): added to the output polynomials.
 static void ks_moddown(fa_ctx* c, const fa::KsItem* ks, int count, const double* const* c0s, double* const* outs,
-                       double* u, double* conv, hipStream_t s, const double* const* b1s = nullptr, int nq = 1) {
+                       double* u, double* conv, hipStream_t s, const double* const* b1s = nullptr, int nq = 1,
+                       const double* const* b0s = nullptr) {
   const size_t n = c->n, L = c->L;
+  if (fa::small_ring(c)) {
+    std::vector<fa::SrItem> it(count);
+    for (int j = 0; j < count; ++j)
+      it[j] = {ks[j].ext, ks[j].c1, ks[j].key, nullptr, ks[j].u, c0s[j],
+               {b0s ? b0s[j] : nullptr, b1s ? b1s[j] : nullptr}, outs[j], (size_t)c->K * n, ks[j].gal};
+    return fa::sr_finish(c, it.data(), count, true, s);
+  }
   if (c->dnum == 1) {
     // one digit: the special-prime sum and the first inverse pass in one
     // kernel (measured faster at 2 and 3 primes; with more digits the fused
@@ -1404,8 +1423,8 @@ static void ks_moddown(fa_ctx* c, const fa::KsItem* ks, int count, const double*
   }
   std::vector<fa::MdKsItem> it(count);
   for (int j = 0; j < count; ++j)
-    it[j] = {conv + (size_t)2 * j * L * n, ks[j].ext, ks[j].c1, ks[j].key, c0s[j], b1s ? b1s[j] : nullptr, outs[j],
-             ks[j].gal};
+    it[j] = {conv + (size_t)2 * j * L * n, ks[j].ext, ks[j].c1, ks[j].key, c0s[j], b0s ? b0s[j] : nullptr,
+             b1s ? b1s[j] : nullptr, outs[j], ks[j].gal, 0u};
   fa::moddown_ks(c, it.data(), count, s, nq);
 }
 
@@ -1464,8 +1483,10 @@ static int rotations_from_ext(fa_ctx* c, const double* q, const double* ext, con
   return check_launch("rotation");
 }
 
-// Full rotation of `nb` ciphertexts by the same step: outs[b] = Rotate(cts[b], step).
-static int rotate_batch(fa_ctx* c, const double* cts, int nb, int step, double* outs, Arena& ar, hipStream_t s) {
+// Full rotation of `nb` ciphertexts by the same step: outs[b] = Rotate(cts[b], step),
+// plus cts[b] when add is set (a fold's step).
+static int rotate_batch(fa_ctx* c, const double* cts, int nb, int step, double* outs, Arena& ar, hipStream_t s,
+                        bool add = false) {
   const size_t n = c->n, L = c->L, np = c->np, dn = c->dnum;
   auto it = c->keys.find(step);
   if (it == c->keys.end()) return fail(FA_E_NOKEY, "no rotation key for step %d", step);
@@ -1478,18 +1499,36 @@ static int rotate_batch(fa_ctx* c, const double* cts, int nb, int step, double* 
   const size_t ctw = 2 * L * n;
   modup(c, cts, ctw, nb, y, L * n, ext, dn * np * n, s);
   std::vector<fa::KsItem> ks(nb);
-  std::vector<const double*> c0s(nb);
+  std::vector<const double*> c0s(nb), c1s(nb);
   std::vector<double*> douts(nb);
   const uint32_t gal = galois(c->n, step);
   for (int b = 0; b < nb; ++b) {
     const double* ct = cts + (size_t)b * ctw;
     ks[b] = {ext + (size_t)b * dn * np * n, ct + L * n, it->second, u + (size_t)b * 2 * np * n, nullptr, gal};
     c0s[b] = ct;
+    c1s[b] = ct + L * n;
     douts[b] = outs + (size_t)b * ctw;
   }
-  ks_moddown(c, ks.data(), nb, c0s.data(), douts.data(), u, conv, s);
+  ks_moddown(c, ks.data(), nb, c0s.data(), douts.data(), u, conv, s, add ? c1s.data() : nullptr, 1,
+             add ? c0s.data() : nullptr);
   ar.used = mark;
   return check_launch("rotate_batch");
+}
+
+// cts <- cts + Rotate(cts, step) for every step in turn, on nb ciphertexts with
+// room for as many in tmp.  The key switch reads its input through the
+// automorphism while it writes, so the sums go back and forth between the two
+// buffers (an odd number of steps ends with one copy).
+static int fold_batch(fa_ctx* c, double* cts, int nb, const std::vector<int>& steps, double* tmp, Arena& ar,
+                      hipStream_t s) {
+  double *cur = cts, *nxt = tmp;
+  for (int step : steps) {
+    if (int rc = rotate_batch(c, cur, nb, step, nxt, ar, s, true)) return rc;
+    std::swap(cur, nxt);
+  }
+  if (cur != cts)
+    HIPCHK(hipMemcpyAsync(cts, cur, (size_t)nb * 2 * c->L * c->n * 8, hipMemcpyDeviceToDevice, s));
+  return FA_OK;
 }
 
 // Relinearisation of `count` three-component ciphertexts d [count][3][L][N]:
@@ -1528,6 +1567,28 @@ static int relin_batch(fa_ctx* c, const double* d, int count, double* out, Arena
   return check_launch("relinearise");
 }
 
+// The baby rotations of nq queries on a small ring: one decomposition per query
+// (ext + j * ext_st), then as many rotations per launch group as it and the
+// scratch y (y_words) take, on the caller's stream alone: a group's launches
+// are short, and events between streams would cost more than they overlap.
+static int baby_small(fa_ctx* c, const double* const* qs, int nq, int B, double* const* qrots, double* ext,
+                      size_t ext_st, double* y, size_t y_words, hipStream_t s) {
+  const size_t n = c->n, L = c->L, ctw = 2 * L * n, item = 2 * (size_t)c->K * n;
+  for (int j = 0; j < nq; ++j) fa::sr_modup(c, qs[j] + L * n, 0, 1, 0, 1, ext + j * ext_st, s);
+  const int cap = (int)std::min<size_t>(FA_MAXSR, y_words / item);
+  std::vector<fa::SrItem> it;
+  for (int b = 1; b < B; ++b)
+    for (int j = 0; j < nq; ++j) {
+      it.push_back({ext + j * ext_st, qs[j] + L * n, c->keys[b], nullptr, y + it.size() * item, qs[j],
+                    {nullptr, nullptr}, qrots[j] + (size_t)(b - 1) * ctw, (size_t)c->K * n, galois(c->n, b)});
+      if ((int)it.size() == cap || (b == B - 1 && j == nq - 1)) {
+        fa::sr_finish(c, it.data(), (int)it.size(), true, s);
+        it.clear();
+      }
+    }
+  return check_launch("baby rotations");
+}
+
 // Baby rotations qrot[b-1] = Rotate(q, b), b = 1..B-1: one shared decomposition
 // of q.c1, rotation batches spread over lanes.
 static int baby_phase(fa_ctx* c, const double* q, int B, double* qrot, Arena& ar, hipStream_t s) {
@@ -1544,6 +1605,10 @@ static int baby_phase(fa_ctx* c, const double* q, int B, double* qrot, Arena& ar
   double* u = ar.take((size_t)lanes * (rup((size_t)rb * 2 * np * n) / 8));
   double* conv = ar.take((size_t)lanes * (rup((size_t)rb * 2 * L * n) / 8));
   if (!y || !ext || !u || !conv) return fail(FA_E_NOMEM, "workspace too small for the baby rotations");
+  if (fa::small_ring(c)) {
+    ar.used = mark;
+    return baby_small(c, &q, 1, B, &qrot, ext, 0, u, (size_t)lanes * (rup((size_t)rb * 2 * np * n) / 8), s);
+  }
   int rc = ensure_lanes(c, lanes);
   if (rc) return rc;
   modup(c, q, ctw, 1, y, L * n, ext, dn * np * n, s);
@@ -1587,6 +1652,10 @@ static int baby_phase_batch(fa_ctx* c, const double* const* qs, int nq, int B, d
   double* u = ar.take((size_t)lanes * u_lane);
   double* conv = ar.take((size_t)lanes * c_lane);
   if (!y || !ext || !u || !conv) return fail(FA_E_NOMEM, "workspace too small for the baby rotations");
+  if (fa::small_ring(c)) {
+    ar.used = mark;
+    return baby_small(c, qs, nq, B, qrots, ext, rup(ext_w) / 8, u, (size_t)lanes * u_lane, s);
+  }
   int rc = ensure_lanes(c, lanes);
   if (rc) return rc;
   for (int j = 0; j < nq; ++j) modup(c, qs[j], ctw, 1, y, L * n, ext + (size_t)j * (rup(ext_w) / 8), ext_w, s);
@@ -1644,7 +1713,7 @@ static int giant_phase(fa_ctx* c, const double* acc, int nb, int G, int B, doubl
   double* usum = ar.take((size_t)cbm * 2 * np * n);
   double* gconv = ar.take((size_t)cbm * 2 * L * n);
   if (!gy || !gext || !usum || !gconv) return fail(FA_E_NOMEM, "workspace too small for the giant steps");
-  int rc = ensure_lanes(c, lanes);
+  int rc = fa::small_ring(c) ? FA_OK : ensure_lanes(c, lanes);
   if (rc) return rc;
   std::vector<const double*> keys(G - 1);
   std::vector<uint32_t> ggal(G - 1);
@@ -1655,6 +1724,20 @@ static int giant_phase(fa_ctx* c, const double* acc, int nb, int G, int B, doubl
   for (int b0 = 0; b0 < nb; b0 += cbm) {
     const int cb = std::min(cbm, nb - b0);
     const double* accb = acc + (size_t)b0 * astride;
+    if (fa::small_ring(c)) {
+      // every (block, giant) in one launch group; the sums over the giants on
+      // every prime, then the special primes' inverse transforms in place
+      fa::sr_modup(c, accb + ctw + L * n, astride, cb, ctw, G - 1, gext, s);
+      fa::sr_giant(c, gext, accb, astride, keys.data(), ggal.data(), cb, G - 1, usum, s);
+      std::vector<fa::SrItem> it(cb);
+      for (int blk = 0; blk < cb; ++blk) {
+        const double* acc0 = accb + (size_t)blk * astride;
+        double* ub = usum + (size_t)blk * 2 * np * n;
+        it[blk] = {nullptr, nullptr, nullptr, ub, ub + L * n, nullptr, {acc0, acc0 + L * n}, outs[b0 + blk], np * n, 1u};
+      }
+      fa::sr_finish(c, it.data(), cb, false, s);
+      continue;
+    }
     // the ModUps of the giant accumulators in as few launch groups as the
     // lanes allow: one per block (over its G-1 giants) when there are fewer
     // blocks than giants, else one per giant (over the blocks)
@@ -2457,8 +2540,8 @@ int fa_membership(fa_ctx* const* levels, int n_levels, const void* q_r, int L_q,
     int e;
     if ((e = chain_mul_rescale(ch, q, q, yb, y, ar_th, s2))) return e;
     for (int r : fold) {
-      if ((e = rotate_batch(cy, yb, 1, r, rb, ar_th, s2))) return e;
-      fa::add_automorph(cy, yb, rb, 2, 1u, s2);
+      if ((e = rotate_batch(cy, yb, 1, r, rb, ar_th, s2, true))) return e;
+      std::swap(yb, rb);
     }
     // u = alpha (y - mid) in [-1, 1]: the factor alpha costs nothing, it is taken
     // into the scale (u at scale y.s / alpha); the shift is an added constant
@@ -2539,10 +2622,12 @@ int fa_rotate_sum(fa_ctx* c, fa_buf* cts_b, int first_shift, int n_steps, void* 
   const int n_cts = (int)cts_b->count;
   void* cts = cts_b->dev;
   if (n_steps < 0 || first_shift < 1) return fail(FA_E_INVAL, "fa_rotate_sum: bad sizes");
+  std::vector<int> steps;
   for (int k = 0; k < n_steps; ++k) {
     const long r = (long)first_shift << k;
     if (r >= c->n / 2) return fail(FA_E_INVAL, "rotation %ld out of [1, N/2)", r);
     if (!c->keys.count((int)r)) return fail(FA_E_NOKEY, "no rotation key for step %ld", r);
+    steps.push_back((int)r);
   }
   const size_t need = fa_workspace_bytes(c, FA_OP_ROTATE_SUM, n_cts, 0, 1);
   if (!ws || ws_bytes < need) return fail(FA_E_NOMEM, "workspace %zu bytes < %zu needed", ws_bytes, need);
@@ -2553,12 +2638,7 @@ int fa_rotate_sum(fa_ctx* c, fa_buf* cts_b, int first_shift, int n_steps, void* 
   double* base = (double*)cts;
   for (int c0 = 0; c0 < n_cts; c0 += kRotBatch) {
     const int nb = std::min(kRotBatch, n_cts - c0);
-    double* cur = base + (size_t)c0 * ctw;
-    for (int k = 0; k < n_steps; ++k) {
-      int rc = rotate_batch(c, cur, nb, first_shift << k, tmp, ar, s);
-      if (rc) return rc;
-      fa::add_automorph(c, cur, tmp, 2 * nb, 1u, s);
-    }
+    if (int rc = fold_batch(c, base + (size_t)c0 * ctw, nb, steps, tmp, ar, s)) return rc;
   }
   return check_launch("fa_rotate_sum");
 }
@@ -2614,13 +2694,11 @@ static int project(fa_ctx* c, const fa_buf* qb, const fa_buf* wb, bool enc, int 
   int rc = enc ? score_diag_enc(c, (const double*)q, (const double* const*)blocks, 1, r, baby_step, (double*)q_r, ar, s)
                : score_diag(c, (const double*)q, (const double* const*)blocks, 1, r, baby_step, (double*)q_r, ar, s);
   if (rc) return rc;
-  for (int k = 0; k < steps; ++k) {
-    Arena ar2{(char*)ws, ws_bytes, 0};
-    double* tmp = ar2.take((fa_ct_bytes(c) / 8));
-    rc = rotate_batch(c, (const double*)q_r, 1, r << k, tmp, ar2, s);
-    if (rc) return rc;
-    fa::add_automorph(c, (double*)q_r, tmp, 2, 1u, s);
-  }
+  std::vector<int> fold(steps);
+  for (int k = 0; k < steps; ++k) fold[k] = r << k;
+  Arena ar2{(char*)ws, ws_bytes, 0};
+  double* tmp = ar2.take((fa_ct_bytes(c) / 8));
+  if ((rc = fold_batch(c, (double*)q_r, 1, fold, tmp, ar2, s))) return rc;
   if ((rc = check_launch(fn))) return rc;
   out_set(c, qrb, 2, 1, qb->log_scale + wb->log_scale);
   return FA_OK;

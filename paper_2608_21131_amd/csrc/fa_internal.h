@@ -60,6 +60,9 @@ struct fa_ctx {
   double* d_twt_inv = nullptr;
   double* d_twr_fwd = nullptr;    // [np][N/256][8]
   double* d_twr_inv = nullptr;
+  // small rings (fa_small.hip): psi^{brev(k)} for every k < N, and of psi^-1
+  double* d_tws_fwd = nullptr;    // [np][N]
+  double* d_tws_inv = nullptr;
   double* d_mu_hat = nullptr;     // [dnum][alpha][np]   (D_i/d_j) mod prime t
   double* d_md_hat = nullptr;     // [K][L]              (P/p_k) mod q_t
   double* d_mu_scale = nullptr;   // [L] device copy of h_mu_scale
@@ -148,7 +151,7 @@ void moddown_fused(const fa_ctx* c, const MdItem* items, int count, hipStream_t 
 
 // ModDown finish of rotations whose key-switch sum on the ciphertext primes is
 // formed in the same kernel (ks_inner then only covers the special primes):
-// out = (sigma(c0) + (u_Q,0 - conv0^) P^-1, b1 + (u_Q,1 - conv1^) P^-1) with
+// out = (sigma(c0) + b0 + (u_Q,0 - conv0^) P^-1, b1 + (u_Q,1 - conv1^) P^-1) with
 // u_Q,h = sum_i sigma(ext_i) key[i][h] and conv (from moddown with pass_b false)
 // holding the first pass of Conv_{P->Q} of both polynomials.
 struct MdKsItem {
@@ -157,7 +160,8 @@ struct MdKsItem {
   const double* c1;    // [L][N] the digits' own limbs
   const double* key;   // [dnum][2][np][N]
   const double* c0;    // [L][N]
-  const double* b1;    // [L][N] or null: added to the second output polynomial
+  const double* b0;    // [L][N] or null: added to the first output polynomial
+  const double* b1;    // [L][N] or null: added to the second
   double* out;         // [2][L][N]
   uint32_t gal;
   uint32_t inv_gal;    // gal^-1 mod 2N (set by the launcher)
@@ -207,6 +211,50 @@ void mac_diag(const fa_ctx* c, const double* const* q, const double* const* qrot
 void mac_diag_ct(const fa_ctx* c, const double* q, const double* qrot, const double* const* blocks, int n_blocks,
                  int B, int G, double* acc, hipStream_t s);
 
+// ---- small rings (fa_small.hip): a limb fits one workgroup ----
+// N = 2^13 is the largest whose limb (72 KB padded) fits a CU's 160 KB of LDS
+// twice.  At 2^14 one workgroup a CU is left and the calls measured between 0.74
+// and 1.23 of the two-pass kernels' speed, 0.93 over ten of them; at 2^10 to
+// 2^13, twenty-four calls ran 1.9 times as fast on average.
+#define FA_SMALL_LOGN 13
+inline bool small_ring(const fa_ctx* c) { return c->logn <= FA_SMALL_LOGN; }
+void sr_tables(const fa_ctx* c, hipStream_t s);  // fills d_tws_fwd / d_tws_inv
+void sr_ntt(const fa_ctx* c, const LimbList& l, bool fwd, hipStream_t s);
+// ModUp of outer * inner polynomials, number o * inner + i at src + o * outer_st +
+// i * inner_st, into ext [outer * inner][dnum][np][N] (NTT form).  A digit's own
+// limbs of ext are scratch: the key-switch kernels read them from the source.
+void sr_modup(const fa_ctx* c, const double* src, size_t outer_st, int outer, size_t inner_st, int inner, double* ext,
+              hipStream_t s);
+// Key switch and ModDown of one ciphertext:
+// out_h = (u_h,Q - NTT(Conv(u_h,P))) P^-1 + [h = 0] sigma(c0) + add_h, where
+// u_h = sum_i sigma(ext_i) key_i[h] (sum true) or u as given (sum false).
+#define FA_MAXSR 40
+struct SrItem {
+  const double* ext;     // [dnum][np][N]
+  const double* c1;      // [L][N] the digits' own limbs
+  const double* key;     // [dnum][2][np][N]
+  const double* u;       // [2][np][N], sum false
+  double* y;             // scratch: K limbs of N words at y and at y + yst
+  const double* c0;      // [L][N] or null
+  const double* add[2];  // [L][N] or null, added to the output polynomials
+  double* out;           // [2][L][N]; no input of the call may overlap it
+  size_t yst;
+  uint32_t gal;
+};
+void sr_finish(const fa_ctx* c, const SrItem* items, int count, bool sum, hipStream_t s);
+// u[blk] = sum over giants g = 1..ng of the key-switch sums of ext[blk][g-1] on every
+// prime, plus P sigma_g(acc_g.c0) (see giant_ks; ext fully transformed)
+#define FA_MAXSRG 256
+void sr_giant(const fa_ctx* c, const double* ext, const double* acc, size_t astride, const double* const* keys,
+              const uint32_t* gals, int nb, int ng, double* u, hipStream_t s);
+// out = (ct - lift of last) q_last^-1 per polynomial; last [n_polys][N] the last limb's
+// coefficients, r.c[t] = q_last^-1 mod q_t
+struct SrRes {
+  double c[16];
+};
+void sr_rescale(const fa_ctx* c, const double* ct, const double* last, int n_polys, double* out, const SrRes& r,
+                hipStream_t s);
+
 // Rescale n_polys polynomials [n_polys][L][N] (NTT form) by the last prime:
 // out [n_polys][L-1][N] = round(x / q_last); scratch: n_polys * L * N words.
 void rescale(const fa_ctx* c, const double* ct, int n_polys, double* out, double* scratch, hipStream_t s);
@@ -242,8 +290,6 @@ void lincomb(const fa_ctx* c, double* out, const double* const* xs, const int* x
 void mul_plain(const fa_ctx* c, const double* ct, const double* const* pts, int count, double* out, hipStream_t s);
 // dst[r] += src[r] for n_limbs limbs of N words, limb r over prime r % period
 void add_limbs(const fa_ctx* c, double* dst, const double* src, int n_limbs, int period, hipStream_t s);
-// dst[i] = dst[i] + sigma_g(src[i]) over `words` words of [.][L][N] data; g = 1 -> plain add
-void add_automorph(const fa_ctx* c, double* dst, const double* src, int n_polys, uint32_t gal, hipStream_t s);
 // residues of signed integers: dst[p][t][k] = src[p][k] mod prime t (t < nprimes)
 void int_to_res(const fa_ctx* c, const int64_t* src, int n_polys, int nprimes, double* dst, hipStream_t s);
 // u64 residues (already < prime) -> words

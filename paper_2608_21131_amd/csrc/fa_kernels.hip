@@ -25,44 +25,10 @@
 #include <mutex>
 #include <type_traits>
 
+#include "fa_arith.h"
 #include "fa_internal.h"
 
 namespace {
-
-__device__ __forceinline__ double reduce(double x, double q, double qinv) {
-  return __fma_rn(-rint(x * qinv), q, x);
-}
-__device__ __forceinline__ double mulc(double a, double w, double wp, double q) {
-  const double h = a * w;
-  const double l = __fma_rn(a, w, -h);
-  const double t = rint(a * wp);
-  return __fma_rn(-t, q, h) + l;
-}
-__device__ __forceinline__ double mul(double a, double b, double q, double qinv) {
-  const double h = a * b;
-  const double l = __fma_rn(a, b, -h);
-  const double t = rint(h * qinv);
-  return __fma_rn(-t, q, h) + l;
-}
-// x in (-q, 2q) -> [0, q)
-__device__ __forceinline__ double canon(double x, double q) {
-  x = x < 0.0 ? x + q : x;
-  return x >= q ? x - q : x;
-}
-// full canonical reduction of |x| < 2^52
-__device__ __forceinline__ double canon_full(double x, double q, double qinv) {
-  x = reduce(x, q, qinv);
-  return x < 0.0 ? x + q : x;
-}
-
-// Index permutation of the Galois automorphism X -> X^gal in NTT order:
-// output slot i of the forward transform holds a(psi^(2 brev(i) + 1)), so
-// sigma(a)^[i] = a^[pi(i)] with 2 brev(pi(i)) + 1 = gal (2 brev(i) + 1) mod 2N.
-__device__ __forceinline__ uint32_t perm(uint32_t i, uint32_t gal, int logn) {
-  const uint32_t e = 2u * (__brev(i) >> (32 - logn)) + 1u;
-  const uint32_t e2 = (gal * e) & ((2u << logn) - 1u);
-  return __brev((e2 - 1u) >> 1) >> (32 - logn);
-}
 
 // Cooley-Tukey butterfly (forward): (x, y) -> (x + w y, x - w y).  With R
 // false x is not reduced first: the passes below reduce on odd stages only.
@@ -539,8 +505,9 @@ template <class St>
 __device__ __forceinline__ void fwd_b_body(double* a, const St& st, const double* __restrict__ T,
                                            const double* __restrict__ F, double q, double qinv, int logn,
                                            double* sm) {
-  const int n = 1 << logn;
-  const int rows = (n >> 8) < 16 ? (n >> 8) : 16;
+  // 16 on every ring that comes here; kept out of the compiler's sight, which
+  // schedules k_giant_ks half as fast when it knows fwd_b_lds's trip counts
+  const int rows = (1 << logn >> 8) < 16 ? (1 << logn >> 8) : 16;
   const int row0 = blockIdx.x * rows;
   fwd_b_lds(a, row0, rows, T, F, q, qinv, sm);
   // out with consecutive threads on consecutive words
@@ -575,7 +542,7 @@ __global__ __launch_bounds__(256) void k_moddown_b(MdArgs args, const DevPrime* 
 // ModDown finish of a rotation with its key-switch sum on the ciphertext
 // primes formed in place: for limb t < L and the tile's words k,
 //   u_h[k] = sum_i sigma(ext_i)[k] * key_i[h][t][k]   (h = 0, 1; own limbs from c1)
-//   out0[k] = c0[pi(k)] + (u_0[k] - conv0^[k]) * P^-1,
+//   out0[k] = c0[pi(k)] + b0[k] + (u_0[k] - conv0^[k]) * P^-1   (b0 = 0 for a rotation),
 //   out1[k] = b1[k] + (u_1[k] - conv1^[k]) * P^-1       (b1 = 0 for a rotation)
 // where conv_h^ is the forward transform of Conv_{P->Q} finished here (pass B).
 // The sums never reach HBM; both polynomials of the rotation share one gather.
@@ -670,7 +637,8 @@ __global__ __launch_bounds__(256) void k_moddown_ks_b(MdKsArgs args, const DevPr
 #pragma unroll
   for (int j = 0; j < ROWS; ++j) {
     const int e = threadIdx.x + 256 * j;
-    const double r = mulc(u0[j] - sm[lds_row(e >> 8, e & 255)], pv, pvp, q) + it.c0[o + perm(k0 + 256u * j, it.gal, logn)];
+    double r = mulc(u0[j] - sm[lds_row(e >> 8, e & 255)], pv, pvp, q) + it.c0[o + perm(k0 + 256u * j, it.gal, logn)];
+    if (it.b0) r += it.b0[o + k0 + 256 * j];
     __builtin_nontemporal_store(canon_full(r, q, qinv), it.out + o + k0 + 256 * j);
   }
   __syncthreads();
@@ -688,9 +656,9 @@ __global__ __launch_bounds__(256) void k_moddown_ks_b(MdKsArgs args, const DevPr
 __global__ __launch_bounds__(256) void k_ntt_inv_b(LimbList ll, const DevPrime* __restrict__ pr,
                                                    const double* __restrict__ twt, const double* __restrict__ twr,
                                                    int logn) {
-  __shared__ double sm[16 * ROWW];
+  constexpr int rows = 16;
+  __shared__ double sm[rows * ROWW];
   const int n = 1 << logn;
-  const int rows = (n >> 8) < 16 ? (n >> 8) : 16;
   const int row0 = blockIdx.x * rows;
   const int pi = ll.prime[blockIdx.y];
   double* a = ll.ptr[blockIdx.y];
@@ -807,7 +775,7 @@ __global__ __launch_bounds__(256) void k_ks_inv_b(KsArgs args, const DevPrime* _
                                                   int logn, int L, int np, int nq, int ngroup) {
   __shared__ double sm[16 * ROWW];
   const int n = 1 << logn;
-  const int rows = (n >> 8) < 16 ? (n >> 8) : 16;
+  constexpr int rows = 16;
   int tile, tr, item;
   if (nq == 1) {
     int src;
@@ -822,9 +790,8 @@ __global__ __launch_bounds__(256) void k_ks_inv_b(KsArgs args, const DevPrime* _
   const double* __restrict__ T = twt + (size_t)t * 256;
   const double* __restrict__ F = twr + (size_t)t * (n >> 8) * 8;
   const int u = threadIdx.x, lh = u & 15, rl = u >> 4, r = tile * rows + rl;
-  const bool active = u < rows * 16;
   double y0[16], y1[16];
-  if (active) {
+  {
     const uint32_t k0 = (uint32_t)r * 256u + 16u * lh;
 #pragma unroll
     for (int m = 0; m < 16; ++m) y0[m] = y1[m] = 0.0;
@@ -853,7 +820,7 @@ __global__ __launch_bounds__(256) void k_ks_inv_b(KsArgs args, const DevPrime* _
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     double x[16];
-    if (active) {
+    {
 #pragma unroll
       for (int m = 0; m < 16; ++m) x[m] = h == 0 ? y0[m] : y1[m];
 #pragma unroll
@@ -870,7 +837,7 @@ __global__ __launch_bounds__(256) void k_ks_inv_b(KsArgs args, const DevPrime* _
       for (int m = 0; m < 16; ++m) sm[lds_row(rl, 16 * lh + m)] = x[m];
     }
     __syncthreads();
-    if (active) {
+    {
 #pragma unroll
       for (int m = 0; m < 16; ++m) x[m] = sm[lds_row(rl, lh + 16 * m)];
 #pragma unroll
@@ -1426,19 +1393,6 @@ __global__ __launch_bounds__(256) void k_mul_plain(const double* __restrict__ ct
   o[ln + f] = canon(mul(ct[ln + f], p, q, qinv), q);
 }
 
-__global__ __launch_bounds__(256) void k_add_automorph(double* __restrict__ dst, const double* __restrict__ src,
-                                                       const DevPrime* __restrict__ pr, int logn, int L,
-                                                       uint32_t gal) {
-  const int n = 1 << logn;
-  const int k = blockIdx.x * 256 + threadIdx.x;
-  const int row = blockIdx.y;  // poly * L + t
-  const int t = row % L;
-  const double q = pr[t].q;
-  const uint32_t kk = gal == 1u ? (uint32_t)k : perm((uint32_t)k, gal, logn);
-  const size_t o = (size_t)row * n;
-  dst[o + k] = canon(dst[o + k] + src[o + kk], q);
-}
-
 __global__ __launch_bounds__(256) void k_add_limbs(double* __restrict__ dst, const double* __restrict__ src,
                                                    const DevPrime* __restrict__ pr, int logn, int period) {
   const int n = 1 << logn;
@@ -1697,27 +1651,22 @@ static void launch_fwd(const fa_ctx* c, const LimbList& l, hipStream_t s) {
   using P = PassA<SA>;
   dim3 ga(c->n / P::TILE, l.n);
   hipLaunchKernelGGL(k_ntt_fwd_a<SA>, ga, dim3(256), 0, s, l, c->d_pr, c->d_twa_fwd);
-  const int rows = (c->n >> 8) < 16 ? (c->n >> 8) : 16;
-  dim3 gb((c->n >> 8) / rows, l.n);
+  dim3 gb((c->n >> 8) / 16, l.n);
   hipLaunchKernelGGL(k_ntt_fwd_b, gb, dim3(256), 0, s, l, c->d_pr, c->d_twt_fwd, c->d_twr_fwd, c->logn);
 }
 
 template <int SA>
 static void launch_inv(const fa_ctx* c, const LimbList& l, hipStream_t s) {
   using P = PassA<SA>;
-  const int rows = (c->n >> 8) < 16 ? (c->n >> 8) : 16;
-  dim3 gb((c->n >> 8) / rows, l.n);
+  dim3 gb((c->n >> 8) / 16, l.n);
   hipLaunchKernelGGL(k_ntt_inv_b, gb, dim3(256), 0, s, l, c->d_pr, c->d_twt_inv, c->d_twr_inv, c->logn);
   dim3 ga(c->n / P::TILE, l.n);
   hipLaunchKernelGGL(k_ntt_inv_a<SA>, ga, dim3(256), 0, s, l, c->d_pr, c->d_twa_inv);
 }
 
+// rings above FA_SMALL_LOGN
 #define FA_SA_SWITCH(fn, ...)            \
   switch (c->logn - 8) {                  \
-    case 2: fn<2>(__VA_ARGS__); break;    \
-    case 3: fn<3>(__VA_ARGS__); break;    \
-    case 4: fn<4>(__VA_ARGS__); break;    \
-    case 5: fn<5>(__VA_ARGS__); break;    \
     case 6: fn<6>(__VA_ARGS__); break;    \
     case 7: fn<7>(__VA_ARGS__); break;    \
     case 8: fn<8>(__VA_ARGS__); break;    \
@@ -1726,18 +1675,19 @@ static void launch_inv(const fa_ctx* c, const LimbList& l, hipStream_t s) {
 
 void ntt_fwd(const fa_ctx* c, const LimbList& l, hipStream_t s) {
   if (l.n == 0) return;
+  if (small_ring(c)) return sr_ntt(c, l, true, s);
   FA_SA_SWITCH(launch_fwd, c, l, s)
 }
 
 void ntt_inv(const fa_ctx* c, const LimbList& l, hipStream_t s) {
   if (l.n == 0) return;
+  if (small_ring(c)) return sr_ntt(c, l, false, s);
   FA_SA_SWITCH(launch_inv, c, l, s)
 }
 
 void ntt_inv_b(const fa_ctx* c, const LimbList& l, hipStream_t s) {
   if (l.n == 0) return;
-  const int rows = (c->n >> 8) < 16 ? (c->n >> 8) : 16;
-  dim3 gb((c->n >> 8) / rows, l.n);
+  dim3 gb((c->n >> 8) / 16, l.n);
   hipLaunchKernelGGL(k_ntt_inv_b, gb, dim3(256), 0, s, l, c->d_pr, c->d_twt_inv, c->d_twr_inv, c->logn);
 }
 
@@ -1804,8 +1754,7 @@ static void modup_pass_b(const fa_ctx* c, const MuItem* items, int count, hipStr
   // second pass over every converted limb
   LimbList l;
   l.n = 0;
-  const int rows = (c->n >> 8) < 16 ? (c->n >> 8) : 16;
-  dim3 gb((c->n >> 8) / rows, 0);
+  dim3 gb((c->n >> 8) / 16, 0);
   auto flush = [&]() {
     if (!l.n) return;
     gb.y = l.n;
@@ -1847,14 +1796,13 @@ static void launch_moddown_fused_sa(const fa_ctx* c, const MdArgs& a, int count,
 }
 
 void moddown_fused(const fa_ctx* c, const MdItem* items, int count, hipStream_t s, bool pass_b) {
-  const int rows = (c->n >> 8) < 16 ? (c->n >> 8) : 16;
   for (int off = 0; off < count; off += FA_MAXMD) {
     const int m = count - off < FA_MAXMD ? count - off : FA_MAXMD;
     MdArgs a;
     for (int i = 0; i < m; ++i) a.it[i] = items[off + i];
     FA_SA_SWITCH(launch_moddown_fused_sa, c, a, m, s)
     if (!pass_b) continue;
-    dim3 gb((c->n >> 8) / rows, c->L, m);
+    dim3 gb((c->n >> 8) / 16, c->L, m);
     hipLaunchKernelGGL(k_moddown_b, gb, dim3(256), 0, s, a, c->d_pr, c->d_twt_fwd, c->d_twr_fwd, c->logn);
   }
 }
@@ -1877,20 +1825,15 @@ static uint32_t inv_galois(uint32_t g, int logn) {
 
 template <int DNUM>
 static void launch_moddown_ks(const fa_ctx* c, const MdKsArgs& a, int m, int nq, hipStream_t s) {
-  // eight 256-word rows per workgroup (four on a ring of 2^10, the smallest
-  // accepted): twice the workgroups of sixteen-row tiles, measured faster at
-  // 8 and 12 primes and even at 3
-  const int rows = (c->n >> 8) < 8 ? (c->n >> 8) : 8;
+  // eight 256-word rows per workgroup: twice the workgroups of sixteen-row tiles,
+  // measured faster at 8 and 12 primes and even at 3
   const int ngroup = m / nq;
-  dim3 gb(ks_grid((c->n >> 8) / rows, c->L, nq, ngroup));
-  if (rows == 8 && nq == 1)
+  dim3 gb(ks_grid((c->n >> 8) / 8, c->L, nq, ngroup));
+  if (nq == 1)
     hipLaunchKernelGGL((k_moddown_ks_b<DNUM, 8, true>), gb, dim3(256), 0, s, a, c->d_pr, c->d_twt_fwd, c->d_twr_fwd,
                        c->logn, c->L, c->np, c->alpha, nq, ngroup);
-  else if (rows == 8)
-    hipLaunchKernelGGL((k_moddown_ks_b<DNUM, 8, false>), gb, dim3(256), 0, s, a, c->d_pr, c->d_twt_fwd,
-                       c->d_twr_fwd, c->logn, c->L, c->np, c->alpha, nq, ngroup);
   else
-    hipLaunchKernelGGL((k_moddown_ks_b<DNUM, 4, false>), gb, dim3(256), 0, s, a, c->d_pr, c->d_twt_fwd,
+    hipLaunchKernelGGL((k_moddown_ks_b<DNUM, 8, false>), gb, dim3(256), 0, s, a, c->d_pr, c->d_twt_fwd,
                        c->d_twr_fwd, c->logn, c->L, c->np, c->alpha, nq, ngroup);
 }
 
@@ -1950,9 +1893,8 @@ void ks_inner(const fa_ctx* c, const KsItem* items, int count, bool accumulate, 
 
 template <int DNUM>
 static void launch_ks_inv_b(const fa_ctx* c, const KsArgs& a, int m, hipStream_t s, int nq) {
-  const int rows = (c->n >> 8) < 16 ? (c->n >> 8) : 16;
   const int ngroup = m / nq;
-  dim3 g(ks_grid((c->n >> 8) / rows, c->K, nq, ngroup));
+  dim3 g(ks_grid((c->n >> 8) / 16, c->K, nq, ngroup));
   hipLaunchKernelGGL(k_ks_inv_b<DNUM>, g, dim3(256), 0, s, a, c->d_pr, c->d_twt_inv, c->d_twr_inv, c->logn, c->L,
                      c->np, nq, ngroup);
 }
@@ -1973,19 +1915,11 @@ void ks_inv_b(const fa_ctx* c, const KsItem* items, int count, hipStream_t s, in
 
 template <int DNUM>
 static void launch_giant(const fa_ctx* c, const GiantArgs& a, hipStream_t s) {
-  const int rows = (c->n >> 8) < 16 ? (c->n >> 8) : 16;
-  const int ntile = (c->n >> 8) / rows;
+  const int ntile = (c->n >> 8) / 16;
   const int rest8 = (ntile * c->np + 7) / 8;
   dim3 g((unsigned)(8 * a.nb * rest8));
-  if (rows == 16)
-    hipLaunchKernelGGL((k_giant_ks<DNUM, 16>), g, dim3(256), 0, s, a, c->d_pr, c->d_twt_fwd, c->d_twr_fwd, c->logn,
-                       c->L, c->np, c->alpha, ntile);
-  else if (rows == 8)
-    hipLaunchKernelGGL((k_giant_ks<DNUM, 8>), g, dim3(256), 0, s, a, c->d_pr, c->d_twt_fwd, c->d_twr_fwd, c->logn,
-                       c->L, c->np, c->alpha, ntile);
-  else
-    hipLaunchKernelGGL((k_giant_ks<DNUM, 4>), g, dim3(256), 0, s, a, c->d_pr, c->d_twt_fwd, c->d_twr_fwd, c->logn,
-                       c->L, c->np, c->alpha, ntile);
+  hipLaunchKernelGGL((k_giant_ks<DNUM, 16>), g, dim3(256), 0, s, a, c->d_pr, c->d_twt_fwd, c->d_twr_fwd, c->logn,
+                     c->L, c->np, c->alpha, ntile);
 }
 
 void giant_ks(const fa_ctx* c, const double* ext, const double* acc, size_t astride, const double* const* keys,
@@ -2191,11 +2125,6 @@ void mul_plain(const fa_ctx* c, const double* ct, const double* const* pts, int 
   }
 }
 
-void add_automorph(const fa_ctx* c, double* dst, const double* src, int n_polys, uint32_t gal, hipStream_t s) {
-  dim3 g(c->n / 256, n_polys * c->L);
-  hipLaunchKernelGGL(k_add_automorph, g, dim3(256), 0, s, dst, src, c->d_pr, c->logn, c->L, gal);
-}
-
 static ResArgs res_args(const fa_ctx* c, const uint64_t* cres, int L) {
   ResArgs a;
   for (int t = 0; t < FA_MAXLIMB; ++t) {
@@ -2214,10 +2143,6 @@ void rescale(const fa_ctx* c, const double* ct, int n_polys, double* out, double
     LimbBatch inv(c, s, false);
     for (int h = 0; h < n_polys; ++h) inv.add(last + (size_t)h * n, L - 1, ct + ((size_t)h * L + L - 1) * n);
   }
-  const double ql = (double)c->primes[L - 1];
-  hipLaunchKernelGGL(k_rescale_lift, dim3(c->n / 256, L - 1, n_polys), dim3(256), 0, s, last, lift, c->d_pr, c->logn,
-                     L - 1, ql);
-  ntt_fwd_strided(c, lift, n, n_polys * (L - 1), L - 1, 0, s);
   std::vector<uint64_t> inv(L - 1);
   const uint64_t qlast = c->primes[L - 1];
   for (int t = 0; t < L - 1; ++t) {
@@ -2230,6 +2155,15 @@ void rescale(const fa_ctx* c, const double* ct, int n_polys, double* out, double
     }
     inv[t] = (uint64_t)r;
   }
+  if (small_ring(c)) {
+    SrRes r{};
+    for (int t = 0; t < L - 1; ++t) r.c[t] = (double)inv[t];
+    return sr_rescale(c, ct, last, n_polys, out, r, s);
+  }
+  const double ql = (double)c->primes[L - 1];
+  hipLaunchKernelGGL(k_rescale_lift, dim3(c->n / 256, L - 1, n_polys), dim3(256), 0, s, last, lift, c->d_pr, c->logn,
+                     L - 1, ql);
+  ntt_fwd_strided(c, lift, n, n_polys * (L - 1), L - 1, 0, s);
   hipLaunchKernelGGL(k_rescale_combine, dim3(c->n / 256, L - 1, n_polys), dim3(256), 0, s, ct, lift, out,
                      res_args(c, inv.data(), L - 1), c->d_pr, c->logn, L);
 }
