@@ -8,7 +8,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libfa.so")
 
-SOURCES = ["fa_kernels.hip", "fa_small.hip", "fa_host.cpp"]
+SOURCES = ["fa_kernels.hip", "fa_small.hip", "fa_encode.hip", "fa_host.cpp"]
 FLAGS = [
     "--offload-arch=gfx950",
     "-O3",

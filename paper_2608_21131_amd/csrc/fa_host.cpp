@@ -34,7 +34,6 @@
 #include <mutex>
 #include <new>
 #include <string>
-#include <thread>
 #include <vector>
 
 #include "fa_internal.h"
@@ -232,23 +231,6 @@ void encode_one(int n, const std::vector<u64>& e, const double* v, int nv, doubl
     out[k] = (int64_t)std::nearbyint(scale * re / (double)n);
   }
 }
-
-template <class F>
-void parallel_for(int count, F f) {
-  int nt = (int)std::thread::hardware_concurrency();
-  nt = std::max(1, std::min(nt, 16));
-  nt = std::min(nt, count);
-  if (nt <= 1) {
-    for (int i = 0; i < count; ++i) f(i);
-    return;
-  }
-  std::vector<std::thread> th;
-  for (int w = 0; w < nt; ++w)
-    th.emplace_back([&, w]() {
-      for (int i = w; i < count; i += nt) f(i);
-    });
-  for (auto& t : th) t.join();
-}
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -372,6 +354,9 @@ void fa_ctx_destroy(fa_ctx* c) {
   (void)hipFree(c->d_twr_inv);
   (void)hipFree(c->d_tws_fwd);
   (void)hipFree(c->d_tws_inv);
+  (void)hipFree(c->d_fft_root);
+  (void)hipFree(c->d_fft_twist);
+  (void)hipFree(c->d_fft_slot);
   (void)hipFree(c->d_mu_hat);
   (void)hipFree(c->d_md_hat);
   (void)hipFree(c->d_mu_scale);
@@ -1149,12 +1134,71 @@ static int upload_int_pts(fa_ctx* c, const int64_t* coeffs, int n_pts, double* p
     const int m = std::min(chunk, n_pts - p0);
     HIPCHK(hipMemcpyAsync(dm, coeffs + (size_t)p0 * n, (size_t)m * n * 8, hipMemcpyHostToDevice, s));
     double* dst = pts + (size_t)p0 * L * n;
-    fa::int_to_res(c, dm, m, (int)L, dst, s);
-    fa::ntt_fwd_strided(c, dst, n, m * (int)L, (int)L, 0, s);
+    fa::int_to_ntt(c, dm, m, dst, s);
     if ((rc = check_launch("encode"))) break;
     HIPCHK(hipStreamSynchronize(s));
   }
   (void)hipFree(dm);
+  return rc;
+}
+
+// The encoders' device tables, from the host's (so that both encode with the
+// same rounded values).
+static int ensure_fft(fa_ctx* c) {
+  std::lock_guard<std::mutex> lock(c->fft_mu);
+  if (c->d_fft_slot) return FA_OK;
+  const FftTables& tb = fft_tables(c->n);
+  const size_t n = c->n;
+  std::vector<uint32_t> slot(n);
+  for (size_t j = 0; j < n / 2; ++j) slot[(tb.e[j] - 1) / 2] = slot[(2 * n - tb.e[j] - 1) / 2] = (uint32_t)j;
+  double *root = nullptr, *twist = nullptr;
+  uint32_t* ds = nullptr;
+  int rc;
+  hipError_t e = hipSuccess;
+  if (!(rc = dev_alloc(&root, n)) && !(rc = dev_alloc(&twist, 2 * n)) && !(rc = dev_alloc(&ds, n))) {
+    e = hipMemcpy(root, tb.root_fwd.data(), n * 8, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(twist, tb.twist.data(), 2 * n * 8, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(ds, slot.data(), n * 4, hipMemcpyHostToDevice);
+    if (e != hipSuccess) rc = fail(FA_E_HIP, "encoding tables: %s", hipGetErrorString(e));
+  }
+  if (rc) {
+    (void)hipFree(root);
+    (void)hipFree(twist);
+    (void)hipFree(ds);
+    return rc;
+  }
+  c->d_fft_root = root;
+  c->d_fft_twist = twist;
+  c->d_fft_slot = ds;
+  return FA_OK;
+}
+
+// Plaintexts of float slots: rows (host, row_words floats) go up once, then
+// n_pts plaintexts in chunks: slots to integers to residues in NTT form.  The
+// transform of the slots uses the plaintexts' own memory (two limbs each) where
+// they have two limbs.
+static int encode_float(fa_ctx* c, fa::EncArgs a, size_t row_words, int n_pts, double* pts, hipStream_t s) {
+  int rc = ensure_fft(c);
+  if (rc) return rc;
+  const size_t n = c->n, L = c->L;
+  const int chunk = std::min(64, n_pts);
+  const size_t rows_b = (row_words * 4 + 255) & ~(size_t)255, ints = (size_t)chunk * n;
+  char* buf = nullptr;
+  if ((rc = dev_alloc(&buf, rows_b + ints * 8 + (L < 2 ? ints * 16 : 0)))) return rc;
+  hipError_t e = hipMemcpyAsync(buf, a.rows, row_words * 4, hipMemcpyHostToDevice, s);
+  if (e != hipSuccess) rc = fail(FA_E_HIP, "encode upload: %s", hipGetErrorString(e));
+  a.rows = (const float*)buf;
+  int64_t* dm = (int64_t*)(buf + rows_b);
+  for (int p0 = 0; p0 < n_pts && !rc; p0 += chunk) {
+    const int m = std::min(chunk, n_pts - p0);
+    double* dst = pts + (size_t)p0 * L * n;
+    if (L < 2) fa::encode_slots(c, a, p0, m, (double*)(dm + ints), 2 * n, dm, std::ldexp(1.0, c->log_scale), s);
+    else fa::encode_slots(c, a, p0, m, dst, L * n, dm, std::ldexp(1.0, c->log_scale), s);
+    fa::int_to_ntt(c, dm, m, dst, s);
+    rc = check_launch("encode");
+  }
+  if ((e = hipStreamSynchronize(s)) != hipSuccess && !rc) rc = fail(FA_E_HIP, "encode: %s", hipGetErrorString(e));
+  (void)hipFree(buf);
   return rc;
 }
 
@@ -1180,45 +1224,22 @@ int fa_encode_db_block(fa_ctx* c, const float* rows, int n_rows, int dim, int d,
   if (d < 1 || (d & (d - 1)) || d > S) return fail(FA_E_SHAPE, "d=%d must be a power of two <= N/2", d);
   if (dim < 1 || dim > d) return fail(FA_E_SHAPE, "dim=%d must be in [1, d=%d]", dim, d);
   if (n_rows < 1) return fail(FA_E_SHAPE, "n_rows must be positive");
-  const std::vector<u64>& e = slot_exps(c->n);
-  const double scale = std::ldexp(1.0, c->log_scale);
-  std::vector<int64_t> coeffs;
-  int n_pts;
+  int n_pts, kind;
   if (layout == FA_LAYOUT_DIAG) {
     if (n_rows > S) return fail(FA_E_SHAPE, "a diagonal block holds at most N/2=%d rows, got %d", S, n_rows);
     if (baby_step < 1 || d % baby_step) return fail(FA_E_INVAL, "baby_step %d must divide d=%d", baby_step, d);
     n_pts = d;
-    if (int rc = out_check(c, pts_b, "fa_encode_db_block", "pts", n_pts, 1)) return rc;
-    coeffs.assign((size_t)n_pts * c->n, 0);
-    parallel_for(n_pts, [&](int j) {
-      const int g = j / baby_step;
-      const int shift = g * baby_step;  // pre-rotation right by gB
-      std::vector<double> v(S, 0.0);
-      for (int i = 0; i < n_rows; ++i) {
-        const int col = (i + j) % d;
-        const double x = col < dim ? (double)rows[(size_t)i * dim + col] : 0.0;
-        v[(i + shift) % S] = x;
-      }
-      encode_one(c->n, e, v.data(), S, scale, coeffs.data() + (size_t)j * c->n);
-    });
+    kind = fa::ENC_DIAG;
   } else if (layout == FA_LAYOUT_ROW) {
     const int per = S / d;
     n_pts = (n_rows + per - 1) / per;
-    if (int rc = out_check(c, pts_b, "fa_encode_db_block", "pts", n_pts, 1)) return rc;
-    coeffs.assign((size_t)n_pts * c->n, 0);
-    parallel_for(n_pts, [&](int w) {
-      std::vector<double> v(S, 0.0);
-      for (int t = 0; t < per; ++t) {
-        const int row = w * per + t;
-        if (row >= n_rows) break;
-        for (int u = 0; u < dim; ++u) v[(size_t)t * d + u] = rows[(size_t)row * dim + u];
-      }
-      encode_one(c->n, e, v.data(), S, scale, coeffs.data() + (size_t)w * c->n);
-    });
+    kind = fa::ENC_ROWS;
   } else {
     return fail(FA_E_INVAL, "unknown layout %d", layout);
   }
-  const int rc = upload_int_pts(c, coeffs.data(), n_pts, (double*)pts_b->dev, (hipStream_t)stream);
+  if (int rc = out_check(c, pts_b, "fa_encode_db_block", "pts", n_pts, 1)) return rc;
+  const int rc = encode_float(c, {rows, kind, n_rows, dim, d, baby_step}, (size_t)n_rows * dim, n_pts,
+                              (double*)pts_b->dev, (hipStream_t)stream);
   if (!rc) out_set(c, pts_b, 1, n_pts, c->log_scale);
   return rc;
 }
@@ -1230,17 +1251,8 @@ int fa_encode_projection(fa_ctx* c, const float* W, int d_in, int r, int baby_st
     return fail(FA_E_SHAPE, "d_in=%d, r=%d: powers of two with r | d_in and d_in <= N/2", d_in, r);
   if (baby_step < 1 || r % baby_step) return fail(FA_E_INVAL, "baby_step %d must divide r=%d", baby_step, r);
   if (int rc = out_check(c, pts, "fa_encode_projection", "pts", r, 1)) return rc;
-  const std::vector<u64>& e = slot_exps(c->n);
-  const double scale = std::ldexp(1.0, c->log_scale);
-  std::vector<int64_t> coeffs((size_t)r * c->n);
-  parallel_for(r, [&](int j) {
-    const int shift = (j / baby_step) * baby_step;  // pre-rotation right by gB
-    std::vector<double> v(S);
-    for (int s = 0; s < S; ++s)
-      v[(s + shift) % S] = (double)W[(size_t)((s + j) % d_in) * r + (s % r)];
-    encode_one(c->n, e, v.data(), S, scale, coeffs.data() + (size_t)j * c->n);
-  });
-  const int rc = upload_int_pts(c, coeffs.data(), r, (double*)pts->dev, (hipStream_t)stream);
+  const int rc = encode_float(c, {W, fa::ENC_PROJ, d_in, r, r, baby_step}, (size_t)d_in * r, r, (double*)pts->dev,
+                              (hipStream_t)stream);
   if (!rc) out_set(c, pts, 1, r, c->log_scale);
   return rc;
 }

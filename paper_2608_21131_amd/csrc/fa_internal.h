@@ -89,6 +89,13 @@ struct fa_ctx {
   // runs there while the scores run on the caller's stream
   hipStream_t side = nullptr;
   hipEvent_t side_fork = nullptr, side_join = nullptr;
+  // tables of the float encoders (built by the first call that needs them):
+  // e^{-2 pi i k / N} for k < N/2 and e^{i pi k / N} for k < N as (re, im) pairs,
+  // and the slot whose value point t of the transform takes
+  std::mutex fft_mu;
+  double* d_fft_root = nullptr;
+  double* d_fft_twist = nullptr;
+  uint32_t* d_fft_slot = nullptr;
   // device staging of fa_decrypt / fa_export_coeffs (client and test side),
   // grown on demand and reused; the mutex serialises callers on other threads
   std::mutex export_mu;
@@ -290,6 +297,17 @@ void lincomb(const fa_ctx* c, double* out, const double* const* xs, const int* x
 void mul_plain(const fa_ctx* c, const double* ct, const double* const* pts, int count, double* out, hipStream_t s);
 // dst[r] += src[r] for n_limbs limbs of N words, limb r over prime r % period
 void add_limbs(const fa_ctx* c, double* dst, const double* src, int n_limbs, int period, hipStream_t s);
+// Integer coefficients of float slots (fa_encode.hip) for plaintexts p0 .. p0+count-1
+// of a layout: out [count][N]; z: 2N words of scratch per plaintext at z + p * zst.
+enum { ENC_DIAG, ENC_ROWS, ENC_PROJ };
+struct EncArgs {
+  const float* rows;  // device: [n_rows][dim], or the projection [n_rows = d_in][d = r]
+  int kind, n_rows, dim, d, B;
+};
+void encode_slots(const fa_ctx* c, const EncArgs& a, int p0, int count, double* z, size_t zst, int64_t* out,
+                  double scale, hipStream_t s);
+// plaintexts (NTT form, every ciphertext prime) of count integer polynomials src [count][N]
+void int_to_ntt(const fa_ctx* c, const int64_t* src, int count, double* dst, hipStream_t s);
 // residues of signed integers: dst[p][t][k] = src[p][k] mod prime t (t < nprimes)
 void int_to_res(const fa_ctx* c, const int64_t* src, int n_polys, int nprimes, double* dst, hipStream_t s);
 // u64 residues (already < prime) -> words

@@ -81,6 +81,17 @@ struct PlainLd {
   const double* src;
   __device__ double operator()(size_t i) const { return src[i]; }
 };
+// v mod q within q/2 + 2^32 for any 64-bit v: the high half times 2^32 is exact in
+// a double and so is its reduction (the quotient is below 2^14).  A 64-bit integer
+// division here takes longer than the pass's eight stages.
+__device__ __forceinline__ double int_residue(int64_t v, double q, double qinv) {
+  return reduce((double)(int32_t)(v >> 32) * 0x1p32, q, qinv) + (double)(uint32_t)v;
+}
+struct IntLd {
+  const int64_t* src;
+  double q, qinv;
+  __device__ double operator()(size_t i) const { return int_residue(src[i], q, qinv); }
+};
 template <int SA, class Ld>
 __device__ __forceinline__ void fwd_a_body(const Ld& ld, double* a, const double* __restrict__ w, double q,
                                            double qinv, int col0, double* sm) {
@@ -133,6 +144,21 @@ __global__ __launch_bounds__(256) void k_ntt_fwd_a(LimbList ll, const DevPrime* 
   const double q = pr[pi].q, qinv = pr[pi].qinv;
   fwd_a_body<SA>(PlainLd{ll.src[blockIdx.y]}, ll.ptr[blockIdx.y], twa + (size_t)pi * 256, q, qinv,
                  blockIdx.x * P::COLS, sm);
+}
+
+// The same pass from integer coefficients, prime t = blockIdx.y of polynomial
+// blockIdx.z: the residues never go through memory.
+template <int SA>
+__global__ __launch_bounds__(256) void k_ntt_fwd_a_int(const int64_t* __restrict__ src, double* __restrict__ dst,
+                                                       const DevPrime* __restrict__ pr,
+                                                       const double* __restrict__ twa, int L) {
+  using P = PassA<SA>;
+  __shared__ double sm[P::TILE];
+  constexpr size_t n = (size_t)P::H << 8;
+  const int t = blockIdx.y;
+  const double q = pr[t].q, qinv = pr[t].qinv;
+  fwd_a_body<SA>(IntLd{src + blockIdx.z * n, q, qinv}, dst + (blockIdx.z * (size_t)L + t) * n, twa + (size_t)t * 256, q,
+                 qinv, blockIdx.x * P::COLS, sm);
 }
 
 // ModUp, first pass: ext[i][t] = pass A of Conv_{digit i -> t}(y), for every
@@ -1551,10 +1577,8 @@ __global__ __launch_bounds__(256) void k_int_to_res(const int64_t* __restrict__ 
   const int k = blockIdx.x * 256 + threadIdx.x;
   const int t = blockIdx.y;
   const int p = blockIdx.z;
-  const int64_t q = (int64_t)pr[t].q;
-  int64_t v = src[(size_t)p * n + k] % q;
-  if (v < 0) v += q;
-  dst[((size_t)p * nprimes + t) * n + k] = (double)v;
+  const double q = pr[t].q, qinv = pr[t].qinv;
+  dst[((size_t)p * nprimes + t) * n + k] = canon_full(int_residue(src[(size_t)p * n + k], q, qinv), q, qinv);
 }
 
 __global__ __launch_bounds__(256) void k_u64_to_res(const uint64_t* __restrict__ src, size_t words,
@@ -2256,6 +2280,33 @@ void int_to_res(const fa_ctx* c, const int64_t* src, int n_polys, int nprimes, d
     dim3 g(c->n / 256, nprimes, m);
     hipLaunchKernelGGL(k_int_to_res, g, dim3(256), 0, s, src + (size_t)p0 * c->n,
                        dst + (size_t)p0 * nprimes * c->n, c->d_pr, c->logn, nprimes);
+  }
+}
+
+template <int SA>
+static void launch_fwd_a_int(const fa_ctx* c, const int64_t* src, int count, double* dst, hipStream_t s) {
+  using P = PassA<SA>;
+  hipLaunchKernelGGL(k_ntt_fwd_a_int<SA>, dim3(c->n / P::TILE, c->L, count), dim3(256), 0, s, src, dst, c->d_pr,
+                     c->d_twa_fwd, c->L);
+}
+void int_to_ntt(const fa_ctx* c, const int64_t* src, int count, double* dst, hipStream_t s) {
+  if (small_ring(c)) {
+    int_to_res(c, src, count, c->L, dst, s);
+    return ntt_fwd_strided(c, dst, c->n, count * c->L, c->L, 0, s);
+  }
+  FA_SA_SWITCH(launch_fwd_a_int, c, src, count, dst, s)
+  LimbList l;
+  l.n = 0;
+  for (int i = 0; i < count * c->L; ++i) {
+    l.ptr[l.n] = dst + (size_t)i * c->n;
+    l.src[l.n] = l.ptr[l.n];
+    l.prime[l.n] = i % c->L;
+    l.scale[l.n] = 0.0;
+    if (++l.n == FA_MAXL || i == count * c->L - 1) {
+      hipLaunchKernelGGL(k_ntt_fwd_b, dim3((c->n >> 8) / 16, l.n), dim3(256), 0, s, l, c->d_pr, c->d_twt_fwd,
+                         c->d_twr_fwd, c->logn);
+      l.n = 0;
+    }
   }
 }
 

@@ -33,7 +33,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 def sources_sha256():
     """sha256 over the library's kernel and host sources (any change voids a traffic summary)."""
     h = hashlib.sha256()
-    for f in ("fa_kernels.hip", "fa_small.hip", "fa_arith.h", "fa_host.cpp", "fa_internal.h"):
+    for f in ("fa_kernels.hip", "fa_small.hip", "fa_encode.hip", "fa_arith.h", "fa_host.cpp", "fa_internal.h"):
         h.update(open(os.path.join(ROOT, "paper_2608_21131_amd", "csrc", f), "rb").read())
     return h.hexdigest()
 
