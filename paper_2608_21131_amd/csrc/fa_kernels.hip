@@ -40,16 +40,21 @@ namespace {
 template <bool R = true>
 __device__ __forceinline__ void ct_bfly(double& x, double& y, double w, double q, double qinv) {
   const double u = R ? reduce(x, q, qinv) : x;
-  const double t = mulc(y, w, w * qinv, q);
+  const double t = mul(y, w, q, qinv);
   x = u + t;
   y = u - t;
 }
-// Gentleman-Sande butterfly (inverse): (x, y) -> (x + y, (x - y) w^-1)
+// Gentleman-Sande butterfly (inverse): (x, y) -> (x + y, (x - y) w^-1).  Inputs
+// within c give a sum within 2c (reduced to 1/2 unless R is false) and a product
+// within 0.5 + 0.75c.  From canonical inputs the row pass leaves its first two
+// stages' sums lazy (2, then 4: products of at most 8q are exact) and reduces
+// from there on: 3.5, 3.13, 2.85, ... towards 2.
+template <bool R = true>
 __device__ __forceinline__ void gs_bfly(double& x, double& y, double winv, double q, double qinv) {
   const double u = x + y;
   const double v = x - y;
-  x = reduce(u, q, qinv);
-  y = mulc(v, winv, winv * qinv, q);
+  x = R ? reduce(u, q, qinv) : u;
+  y = mul(v, winv, q, qinv);
 }
 
 // ---------------------------------------------------------------------------
@@ -181,71 +186,157 @@ struct MuArgs {
 //
 // Src describes the group: nl source limbs src(j) over primes sprime(j) with
 // scales scale(j); ntarget targets, the k-th over prime target(k), with
-// conversion factors hat(j, t), written to out(t).
+// conversion factors hat(j, t), written to out(t); CENTRE takes the sources'
+// representatives around 0 instead of canonical ones.
+//
+// 512 threads hold eight words each, so the columns take two or three passes of
+// two or three stages with an LDS exchange between them.  (With sixteen words on
+// 256 threads, one exchange, the kept coefficients took 232-256 registers and
+// two waves per SIMD; eight words leave room for four.)
+template <int SA>
+struct ColPass {
+  static constexpr int H = 1 << SA, COLS = 4096 >> SA, T = 512;
+  static constexpr int PASSES = SA > 6 ? 3 : 2;
+  static constexpr int stages(int p) { return SA == 8 ? (p < 2 ? 3 : 2) : SA == 7 ? (p < 1 ? 3 : 2) : 3; }
+  static constexpr int first(int p) { return p == 0 ? 0 : first(p - 1) + stages(p - 1); }
+  // row group of unit v and the row of its element m in pass p
+  template <int P>
+  static __device__ __forceinline__ int group(int v) {
+    return ((int)threadIdx.x + T * v) / COLS;
+  }
+  template <int P>
+  static __device__ __forceinline__ int row(int v, int m) {
+    constexpr int R = stages(P), ls = SA - first(P) - R;
+    const int g = group<P>(v);
+    return ((g >> ls) << (ls + R)) + (g & ((1 << ls) - 1)) + (m << ls);
+  }
+  // LDS word of a row's column: rows 4 or 8 apart land on the other half of the
+  // banks (a half-wave reads two 16-word pieces at COLS = 16)
+  static __device__ __forceinline__ int lds(int row) {
+    const int a = row * COLS + (int)threadIdx.x % COLS;
+    return a ^ (((a >> 2) ^ (a >> 3)) & 16);
+  }
+  // the first twiddle of stage s1 of pass p for unit v: one per wave where a wave
+  // lies inside a block of rows
+  template <int P>
+  static __device__ __forceinline__ int tw(int v, int s1) {
+    constexpr int S = first(P), R = stages(P), ls = SA - S - R;
+    if constexpr (S == 0) return 1 << s1;
+    const int blk = group<P>(v) >> ls;
+    constexpr bool uniform = (COLS << ls) >= 64;
+    return (1 << (S + s1)) + ((uniform ? __builtin_amdgcn_readfirstlane(blk) : blk) << s1);
+  }
+};
+// Does forward column stage s reduce its first operand?  From |x| <= q/2 (a
+// reduced conversion); the row pass takes inputs within 5.3 q, see ct_bfly.
+constexpr bool col_reduces(int s) {
+  double c = 0.5;
+  for (int i = 0;; ++i) {
+    const bool r = 1.375 * c + 0.5 > 5.3;
+    if (i == s) return r;
+    c = r ? 1.0 + 0.375 * c : 1.375 * c + 0.5;
+  }
+}
+template <int SA, int P>
+__device__ __forceinline__ void col_put(const double (&x)[8], double* sm) {
+  using C = ColPass<SA>;
+  constexpr int E = 1 << C::stages(P);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) sm[C::lds(C::template row<P>(e / E, e % E))] = x[e];
+}
+template <int SA, int P>
+__device__ __forceinline__ void col_get(double (&x)[8], const double* sm) {
+  using C = ColPass<SA>;
+  constexpr int E = 1 << C::stages(P);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) x[e] = sm[C::lds(C::template row<P>(e / E, e % E))];
+}
+template <int SA, int P>
+__device__ __forceinline__ void col_fwd(double (&x)[8], const double* __restrict__ w, double q, double qinv) {
+  using C = ColPass<SA>;
+  constexpr int S = C::first(P), R = C::stages(P), E = 1 << R;
+#pragma unroll
+  for (int s1 = 0; s1 < R; ++s1)
+#pragma unroll
+    for (int v = 0; v < 8 / E; ++v) {
+      const int half = E >> (s1 + 1);
+      const double* __restrict__ ws = w + C::template tw<P>(v, s1);
+#pragma unroll
+      for (int m = 0; m < E; ++m) {
+        if (m & half) continue;
+        if (col_reduces(S + s1)) ct_bfly<true>(x[v * E + m], x[v * E + m + half], ws[m >> (R - s1)], q, qinv);
+        else ct_bfly<false>(x[v * E + m], x[v * E + m + half], ws[m >> (R - s1)], q, qinv);
+      }
+    }
+}
+template <int SA, int P>
+__device__ __forceinline__ void col_inv(double (&x)[8], const double* __restrict__ w, double q, double qinv) {
+  using C = ColPass<SA>;
+  constexpr int R = C::stages(P), E = 1 << R;
+#pragma unroll
+  for (int s1 = R - 1; s1 >= 0; --s1)
+#pragma unroll
+    for (int v = 0; v < 8 / E; ++v) {
+      const int half = E >> (s1 + 1);
+      const double* __restrict__ ws = w + C::template tw<P>(v, s1);
+#pragma unroll
+      for (int m = 0; m < E; ++m) {
+        if (m & half) continue;
+        gs_bfly(x[v * E + m], x[v * E + m + half], ws[m >> (R - s1)], q, qinv);
+      }
+    }
+}
+// all passes; x starts in pass P's layout and ends in the last (first) one's
+template <int SA, int P = 0>
+__device__ __forceinline__ void col_fwd_all(double (&x)[8], const double* __restrict__ w, double q, double qinv,
+                                            double* sm) {
+  col_fwd<SA, P>(x, w, q, qinv);
+  if constexpr (P + 1 < ColPass<SA>::PASSES) {
+    col_put<SA, P>(x, sm);
+    __syncthreads();
+    col_get<SA, P + 1>(x, sm);
+    col_fwd_all<SA, P + 1>(x, w, q, qinv, sm);
+  }
+}
+template <int SA, int P = ColPass<SA>::PASSES - 1>
+__device__ __forceinline__ void col_inv_all(double (&x)[8], const double* __restrict__ w, double q, double qinv,
+                                            double* sm) {
+  col_inv<SA, P>(x, w, q, qinv);
+  if constexpr (P > 0) {
+    col_put<SA, P>(x, sm);
+    __syncthreads();
+    col_get<SA, P - 1>(x, sm);
+    col_inv_all<SA, P - 1>(x, w, q, qinv, sm);
+  }
+}
+
 template <int SA, int NS, class Src>
 __device__ __forceinline__ void conv_fused_body(const Src& sr, const DevPrime* __restrict__ pr,
                                                 const double* __restrict__ twa_f, const double* __restrict__ twa_i,
                                                 int grp, int ngrp, double* sm) {
-  using P = PassA<SA>;
-  constexpr int NU = P::TILE / P::E1 / 256;   // tile units per thread in the E1 layout
-  constexpr int NU2 = P::TILE / P::E2 / 256;  // ... in the E2 layout
-  static_assert(NU * P::E1 * 256 == P::TILE && NU2 * P::E2 * 256 == P::TILE, "whole units per thread");
+  using C = ColPass<SA>;
+  constexpr int PL = C::PASSES - 1, EL = 1 << C::stages(PL);
   const int nl = sr.nl;
-  const int col0 = blockIdx.x * P::COLS;
-  double y[NS][NU][P::E1];
+  const int col = blockIdx.x * C::COLS + (int)threadIdx.x % C::COLS;
+  double y[NS][8];
+#pragma unroll
+  for (int j = 0; j < NS; ++j)
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      y[j][e] = j < nl ? sr.src(j)[((size_t)C::template row<PL>(e / EL, e % EL) << 8) + col] : 0.0;
 #pragma unroll
   for (int j = 0; j < NS; ++j) {
     if (j < nl) {
       const int pj = sr.sprime(j);
       const double q = pr[pj].q, qinv = pr[pj].qinv;
-      const double* __restrict__ w = twa_i + (size_t)pj * 256;
-      const double* __restrict__ a = sr.src(j);
-#pragma unroll
-      for (int v = 0; v < NU2; ++v) {
-        const int u = threadIdx.x + 256 * v;
-        const int c = u % P::COLS, hh = u / P::COLS;
-        double x[P::E2];
-#pragma unroll
-        for (int m = 0; m < P::E2; ++m) x[m] = a[((size_t)((hh << P::S2) + m) << 8) + col0 + c];
-#pragma unroll
-        for (int s2 = P::S2 - 1; s2 >= 0; --s2) {
-          const int st = P::S1 + s2, half = P::E2 >> (s2 + 1);
-#pragma unroll
-          for (int m = 0; m < P::E2; ++m) {
-            if (m & half) continue;
-            gs_bfly(x[m], x[m + half], w[(1 << st) + (hh << s2) + (m >> (P::S2 - s2))], q, qinv);
-          }
-        }
-#pragma unroll
-        for (int m = 0; m < P::E2; ++m) sm[((hh << P::S2) + m) * P::COLS + c] = x[m];
-      }
-      __syncthreads();
+      col_inv_all<SA>(y[j], twa_i + (size_t)pj * 256, q, qinv, sm);
       const double sc = sr.scale(j), scp = sc * qinv;
 #pragma unroll
-      for (int v = 0; v < NU; ++v) {
-        const int u = threadIdx.x + 256 * v;
-        const int c = u % P::COLS, hl = u / P::COLS;
-        double x[P::E1];
-#pragma unroll
-        for (int m = 0; m < P::E1; ++m) x[m] = sm[(hl + (m << P::S2)) * P::COLS + c];
-#pragma unroll
-        for (int st = P::S1 - 1; st >= 0; --st) {
-          const int half = P::E1 >> (st + 1);
-#pragma unroll
-          for (int m = 0; m < P::E1; ++m) {
-            if (m & half) continue;
-            gs_bfly(x[m], x[m + half], w[(1 << st) + (m >> (P::S1 - st))], q, qinv);
-          }
-        }
-#pragma unroll
-        for (int m = 0; m < P::E1; ++m) y[j][v][m] = canon_full(mulc(x[m], sc, scp, q), q, qinv);
+      for (int e = 0; e < 8; ++e) {
+        y[j][e] = canon_full(mulc(y[j][e], sc, scp, q), q, qinv);
+        if (Src::CENTRE && y[j][e] > 0.5 * (q - 1.0)) y[j][e] -= q;
       }
       __syncthreads();  // the next limb reuses the LDS tile
-    } else {
-#pragma unroll
-      for (int v = 0; v < NU; ++v)
-#pragma unroll
-        for (int m = 0; m < P::E1; ++m) y[j][v][m] = 0.0;
     }
   }
   const int per = (sr.ntarget + ngrp - 1) / ngrp;  // targets of this group: k0 <= k < k0 + per
@@ -260,54 +351,18 @@ __device__ __forceinline__ void conv_fused_body(const Src& sr, const DevPrime* _
       h[j] = j < nl ? sr.hat(j, t) : 0.0;
       hp[j] = h[j] * qinv;
     }
-    const double* __restrict__ w = twa_f + (size_t)t * 256;
-    double* __restrict__ a = sr.out(t);
+    double x[8];
 #pragma unroll
-    for (int v = 0; v < NU; ++v) {
-      const int u = threadIdx.x + 256 * v;
-      const int c = u % P::COLS, hl = u / P::COLS;
-      double x[P::E1];
+    for (int e = 0; e < 8; ++e) {
+      double acc = 0.0;
 #pragma unroll
-      for (int m = 0; m < P::E1; ++m) {
-        double acc = 0.0;
-#pragma unroll
-        for (int j = 0; j < NS; ++j) acc += mulc(y[j][v][m], h[j], hp[j], q);
-        x[m] = reduce(acc, q, qinv);
-      }
-#pragma unroll
-      for (int st = 0; st < P::S1; ++st) {
-        const int half = P::E1 >> (st + 1);
-#pragma unroll
-        for (int m = 0; m < P::E1; ++m) {
-          if (m & half) continue;
-          if (st & 1) ct_bfly<true>(x[m], x[m + half], w[(1 << st) + (m >> (P::S1 - st))], q, qinv);
-          else ct_bfly<false>(x[m], x[m + half], w[(1 << st) + (m >> (P::S1 - st))], q, qinv);
-        }
-      }
-#pragma unroll
-      for (int m = 0; m < P::E1; ++m) sm[(hl + (m << P::S2)) * P::COLS + c] = x[m];
+      for (int j = 0; j < NS; ++j) acc += mulc(y[j][e], h[j], hp[j], q);
+      x[e] = reduce(acc, q, qinv);
     }
-    __syncthreads();
+    col_fwd_all<SA>(x, twa_f + (size_t)t * 256, q, qinv, sm);
+    double* __restrict__ a = sr.out(t) + col;
 #pragma unroll
-    for (int v = 0; v < NU2; ++v) {
-      const int u = threadIdx.x + 256 * v;
-      const int c = u % P::COLS, hh = u / P::COLS;
-      double x[P::E2];
-#pragma unroll
-      for (int m = 0; m < P::E2; ++m) x[m] = sm[((hh << P::S2) + m) * P::COLS + c];
-#pragma unroll
-      for (int s2 = 0; s2 < P::S2; ++s2) {
-        const int st = P::S1 + s2, half = P::E2 >> (s2 + 1);
-#pragma unroll
-        for (int m = 0; m < P::E2; ++m) {
-          if (m & half) continue;
-          if (st & 1) ct_bfly<true>(x[m], x[m + half], w[(1 << st) + (hh << s2) + (m >> (P::S2 - s2))], q, qinv);
-          else ct_bfly<false>(x[m], x[m + half], w[(1 << st) + (hh << s2) + (m >> (P::S2 - s2))], q, qinv);
-        }
-      }
-#pragma unroll
-      for (int m = 0; m < P::E2; ++m) a[((size_t)((hh << P::S2) + m) << 8) + col0 + c] = x[m];
-    }
+    for (int e = 0; e < 8; ++e) a[(size_t)C::template row<PL>(e / EL, e % EL) << 8] = x[e];
     __syncthreads();  // the next target reuses the LDS tile
   }
 }
@@ -320,6 +375,7 @@ struct MuSrc {
   const double* hatt;  // [dnum][alpha][np]
   const double* sct;   // [L]
   int i, alpha, lo, nl, n, np, ntarget;
+  static constexpr bool CENTRE = false;
   __device__ const double* src(int j) const { return y + (size_t)(lo + j) * n; }
   __device__ int sprime(int j) const { return lo + j; }
   __device__ double scale(int j) const { return sct[lo + j]; }
@@ -334,6 +390,7 @@ struct MdSrc {
   const double* hatt;  // [K][L]
   const double* sct;   // [K]
   int L, nl, n, ntarget;
+  static constexpr bool CENTRE = false;
   __device__ const double* src(int j) const { return yP + (size_t)j * n; }
   __device__ int sprime(int j) const { return L + j; }
   __device__ double scale(int j) const { return sct[j]; }
@@ -342,8 +399,23 @@ struct MdSrc {
   __device__ double* out(int t) const { return conv + (size_t)t * n; }
 };
 
+// Rescale sources: the last ciphertext limb, centred, lifted to the others
+struct RsSrc {
+  const double* last;  // [N], row pass of the inverse done
+  double* lift;        // [L-1][N]
+  double ninv;
+  int nl, prime, n, ntarget;
+  static constexpr bool CENTRE = true;
+  __device__ const double* src(int) const { return last; }
+  __device__ int sprime(int) const { return prime; }
+  __device__ double scale(int) const { return ninv; }
+  __device__ int target(int k) const { return k; }
+  __device__ double hat(int, int) const { return 1.0; }
+  __device__ double* out(int t) const { return lift + (size_t)t * n; }
+};
+
 template <int SA, int ALPHA>
-__global__ __launch_bounds__(256) void k_modup_fused(MuArgs args, const DevPrime* __restrict__ pr,
+__global__ __launch_bounds__(512, 4) void k_modup_fused(MuArgs args, const DevPrime* __restrict__ pr,
                                                      const double* __restrict__ twa_f,
                                                      const double* __restrict__ twa_i,
                                                      const double* __restrict__ hat,
@@ -372,7 +444,7 @@ struct MdArgs {
 };
 
 template <int SA, int KP>
-__global__ __launch_bounds__(256, 2) void k_moddown_fused(MdArgs args, const DevPrime* __restrict__ pr,
+__global__ __launch_bounds__(512, 4) void k_moddown_fused(MdArgs args, const DevPrime* __restrict__ pr,
                                                        const double* __restrict__ twa_f,
                                                        const double* __restrict__ twa_i,
                                                        const double* __restrict__ hat,
@@ -390,6 +462,19 @@ __global__ __launch_bounds__(256, 2) void k_moddown_fused(MdArgs args, const Dev
   sr.n = 1 << logn;
   sr.ntarget = L;
   conv_fused_body<SA, KP>(sr, pr, twa_f, twa_i, blockIdx.y, ngrp, sm);
+}
+
+// Rescale, first pass: lift[h][t] = pass A of the last limb's centred lift
+template <int SA>
+__global__ __launch_bounds__(512, 4) void k_rescale_fused(const double* __restrict__ last, double* lift,
+                                                          const DevPrime* __restrict__ pr,
+                                                          const double* __restrict__ twa_f,
+                                                          const double* __restrict__ twa_i, int L, int ngrp) {
+  __shared__ double sm[PassA<SA>::TILE];
+  constexpr int n = 1 << (SA + 8);
+  const size_t h = blockIdx.z;
+  conv_fused_body<SA, 1>(RsSrc{last + h * n, lift + h * (L - 1) * n, pr[L - 1].ninv, 1, L - 1, n, L - 1}, pr, twa_f,
+                         twa_i, blockIdx.y, ngrp, sm);
 }
 
 // inverse pass A (the last pass of the inverse transform): columns; the final
@@ -678,61 +763,63 @@ __global__ __launch_bounds__(256) void k_moddown_ks_b(MdKsArgs args, const DevPr
   }
 }
 
-// inverse pass B (the first pass of the inverse transform), src -> ptr
+// Inverse pass B (the first pass of the inverse transform) of the 16 rows of sm
+// (lds_row layout, canonical words, synchronised) into a: a thread transforms 16
+// consecutive words, then 16 words 16 apart.  The rows come through LDS because
+// 16 consecutive words a lane straight from memory are 64 lines an instruction.
+__device__ __forceinline__ void inv_b_rows(double* sm, double* __restrict__ a, int row0, const double* __restrict__ T,
+                                           const double* __restrict__ F, double q, double qinv) {
+  const int l = threadIdx.x & 15, rl = threadIdx.x >> 4, r = row0 + rl;
+  double x[16];
+#pragma unroll
+  for (int m = 0; m < 16; ++m) x[m] = sm[lds_row(rl, 16 * l + m)];
+#pragma unroll
+  for (int s1 = 7; s1 >= 4; --s1) {
+    const int half = 8 >> (s1 - 4);
+    const double f = F[r * 8 + s1];
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      if (m & half) continue;
+      const double w = twb(T, f, s1, (l << (s1 - 4)) + (m >> (8 - s1)), q, qinv);
+      if (s1 >= 6) gs_bfly<false>(x[m], x[m + half], w, q, qinv);
+      else gs_bfly<true>(x[m], x[m + half], w, q, qinv);
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < 16; ++m) sm[lds_row(rl, 16 * l + m)] = x[m];
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < 16; ++m) x[m] = sm[lds_row(rl, l + 16 * m)];
+#pragma unroll
+  for (int s1 = 3; s1 >= 0; --s1) {
+    const int half = 8 >> s1;
+    const double f = F[r * 8 + s1];
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      if (m & half) continue;
+      gs_bfly(x[m], x[m + half], twb(T, f, s1, m >> (4 - s1), q, qinv), q, qinv);
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < 16; ++m) a[(size_t)r * 256 + l + 16 * m] = x[m];
+}
+
+// src -> ptr
 __global__ __launch_bounds__(256) void k_ntt_inv_b(LimbList ll, const DevPrime* __restrict__ pr,
                                                    const double* __restrict__ twt, const double* __restrict__ twr,
                                                    int logn) {
-  constexpr int rows = 16;
-  __shared__ double sm[rows * ROWW];
-  const int n = 1 << logn;
-  const int row0 = blockIdx.x * rows;
+  __shared__ double sm[16 * ROWW];
+  const int row0 = blockIdx.x * 16;
   const int pi = ll.prime[blockIdx.y];
-  double* a = ll.ptr[blockIdx.y];
   const double q = pr[pi].q, qinv = pr[pi].qinv;
-  const double* __restrict__ T = twt + (size_t)pi * 256;
-  const double* __restrict__ F = twr + (size_t)pi * (n >> 8) * 8;
-  for (int u = threadIdx.x; u < rows * 16; u += 256) {
-    const int lh = u & 15, rl = u >> 4, r = row0 + rl;
-    double x[16];
-    const double2* src = reinterpret_cast<const double2*>(ll.src[blockIdx.y] + (size_t)r * 256 + 16 * lh);
+  const double* __restrict__ src = ll.src[blockIdx.y] + (size_t)row0 * 256 + threadIdx.x;
+  double x[16];
 #pragma unroll
-    for (int m = 0; m < 8; ++m) {
-      const double2 v = src[m];
-      x[2 * m] = v.x;
-      x[2 * m + 1] = v.y;
-    }
+  for (int j = 0; j < 16; ++j) x[j] = src[256 * j];
 #pragma unroll
-    for (int s1 = 7; s1 >= 4; --s1) {
-      const int half = 8 >> (s1 - 4);
-      const double f = F[r * 8 + s1];
-#pragma unroll
-      for (int m = 0; m < 16; ++m) {
-        if (m & half) continue;
-        gs_bfly(x[m], x[m + half], twb(T, f, s1, (lh << (s1 - 4)) + (m >> (8 - s1)), q, qinv), q, qinv);
-      }
-    }
-#pragma unroll
-    for (int m = 0; m < 16; ++m) sm[lds_row(rl, 16 * lh + m)] = x[m];
-  }
+  for (int j = 0; j < 16; ++j) sm[lds_row(j, threadIdx.x)] = x[j];
   __syncthreads();
-  for (int u = threadIdx.x; u < rows * 16; u += 256) {
-    const int l0 = u & 15, rl = u >> 4, r = row0 + rl;
-    double x[16];
-#pragma unroll
-    for (int m = 0; m < 16; ++m) x[m] = sm[lds_row(rl, l0 + 16 * m)];
-#pragma unroll
-    for (int s1 = 3; s1 >= 0; --s1) {
-      const int half = 8 >> s1;
-      const double f = F[r * 8 + s1];
-#pragma unroll
-      for (int m = 0; m < 16; ++m) {
-        if (m & half) continue;
-        gs_bfly(x[m], x[m + half], twb(T, f, s1, m >> (4 - s1), q, qinv), q, qinv);
-      }
-    }
-#pragma unroll
-    for (int m = 0; m < 16; ++m) a[(size_t)r * 256 + l0 + 16 * m] = x[m];
-  }
+  inv_b_rows(sm, ll.ptr[blockIdx.y], row0, twt + (size_t)pi * 256, twr + (size_t)pi * (1 << logn >> 8) * 8, q, qinv);
 }
 
 // ---------------------------------------------------------------------------
@@ -790,24 +877,23 @@ __global__ __launch_bounds__(256) void k_ks_inner(KsArgs args, const DevPrime* _
 }
 
 // Key-switch sum on the special primes fused with the first pass of its
-// inverse transform: for special prime t and the workgroup's rows,
-//   u_h = sum_i sigma(ext_i) * key_i[h]   (h = 0, 1; canonical residues)
-// formed word by word, then the eight stages of inverse pass B in registers
-// and LDS, written to it.u in place of k_ks_inner's output after
-// k_ntt_inv_b.  Sixteen threads per row, sixteen consecutive words each.
-template <int DNUM>
+// inverse transform: for special prime t and the workgroup's 16 rows,
+//   u_h = sum_i sigma(ext_i) * key_i[h]   (h = 0, 1)
+// formed with consecutive threads on consecutive words, each polynomial then
+// through LDS and inverse pass B into it.u, in place of k_ks_inner's sums after
+// k_ntt_inv_b.
+template <int DNUM, bool NT>
 __global__ __launch_bounds__(256) void k_ks_inv_b(KsArgs args, const DevPrime* __restrict__ pr,
                                                   const double* __restrict__ twt, const double* __restrict__ twr,
                                                   int logn, int L, int np, int nq, int ngroup) {
   __shared__ double sm[16 * ROWW];
   const int n = 1 << logn;
-  constexpr int rows = 16;
   int tile, tr, item;
   if (nq == 1) {
     int src;
-    if (!ks_decode_src(blockIdx.x, (n >> 8) / rows, np - L, ngroup, src, tr, item)) return;
-    tile = (int)(perm((uint32_t)src * (uint32_t)(rows * 256), args.it[item].inv_gal, logn) / (uint32_t)(rows * 256));
-  } else if (!ks_decode(blockIdx.x, (n >> 8) / rows, np - L, nq, ngroup, tile, tr, item)) {
+    if (!ks_decode_src(blockIdx.x, n >> 12, np - L, ngroup, src, tr, item)) return;
+    tile = (int)(perm((uint32_t)src << 12, args.it[item].inv_gal, logn) >> 12);
+  } else if (!ks_decode(blockIdx.x, n >> 12, np - L, nq, ngroup, tile, tr, item)) {
     return;
   }
   const int t = L + tr;
@@ -815,73 +901,34 @@ __global__ __launch_bounds__(256) void k_ks_inv_b(KsArgs args, const DevPrime* _
   const double q = pr[t].q, qinv = pr[t].qinv;
   const double* __restrict__ T = twt + (size_t)t * 256;
   const double* __restrict__ F = twr + (size_t)t * (n >> 8) * 8;
-  const int u = threadIdx.x, lh = u & 15, rl = u >> 4, r = tile * rows + rl;
+  const uint32_t k0 = ((uint32_t)tile << 12) + threadIdx.x;  // this thread's words: k0 + 256 j
   double y0[16], y1[16];
-  {
-    const uint32_t k0 = (uint32_t)r * 256u + 16u * lh;
 #pragma unroll
-    for (int m = 0; m < 16; ++m) y0[m] = y1[m] = 0.0;
+  for (int j = 0; j < 16; ++j) y0[j] = y1[j] = 0.0;
 #pragma unroll 1
-    for (int i = 0; i < DNUM; ++i) {
-      const double* __restrict__ src = it.ext + ((size_t)i * np + t) * n;
-      const double2* kb = reinterpret_cast<const double2*>(it.key + (((size_t)i * 2 + 0) * np + t) * n + k0);
-      const double2* ka = reinterpret_cast<const double2*>(it.key + (((size_t)i * 2 + 1) * np + t) * n + k0);
+  for (int i = 0; i < DNUM; ++i) {
+    const double* __restrict__ src = it.ext + ((size_t)i * np + t) * n;
+    const double* __restrict__ kb = it.key + (((size_t)i * 2 + 0) * np + t) * n + k0;
+    const double* __restrict__ ka = it.key + (((size_t)i * 2 + 1) * np + t) * n + k0;
 #pragma unroll
-      for (int m2 = 0; m2 < 8; ++m2) {
-        const double2 b = kb[m2], a = ka[m2];
-        const double x0 = src[perm(k0 + 2u * m2, it.gal, logn)];
-        const double x1 = src[perm(k0 + 2u * m2 + 1u, it.gal, logn)];
-        y0[2 * m2] += mul(x0, b.x, q, qinv);
-        y1[2 * m2] += mul(x0, a.x, q, qinv);
-        y0[2 * m2 + 1] += mul(x1, b.y, q, qinv);
-        y1[2 * m2 + 1] += mul(x1, a.y, q, qinv);
-      }
-    }
-#pragma unroll
-    for (int m = 0; m < 16; ++m) {
-      y0[m] = canon_full(y0[m], q, qinv);
-      y1[m] = canon_full(y1[m], q, qinv);
+    for (int j = 0; j < 16; ++j) {
+      const double x = src[perm(k0 + 256u * j, it.gal, logn)];
+      const double b = NT ? __builtin_nontemporal_load(kb + 256 * j) : kb[256 * j];
+      const double a = NT ? __builtin_nontemporal_load(ka + 256 * j) : ka[256 * j];
+      y0[j] += mul(x, b, q, qinv);
+      y1[j] += mul(x, a, q, qinv);
     }
   }
+  double* out = it.u + (size_t)t * n;
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    double x[16];
-    {
+  for (int j = 0; j < 16; ++j) sm[lds_row(j, threadIdx.x)] = reduce(y0[j], q, qinv);
+  __syncthreads();
+  inv_b_rows(sm, out, tile * 16, T, F, q, qinv);
+  __syncthreads();  // the second polynomial reuses the LDS rows
 #pragma unroll
-      for (int m = 0; m < 16; ++m) x[m] = h == 0 ? y0[m] : y1[m];
-#pragma unroll
-      for (int s1 = 7; s1 >= 4; --s1) {
-        const int half = 8 >> (s1 - 4);
-        const double f = F[r * 8 + s1];
-#pragma unroll
-        for (int m = 0; m < 16; ++m) {
-          if (m & half) continue;
-          gs_bfly(x[m], x[m + half], twb(T, f, s1, (lh << (s1 - 4)) + (m >> (8 - s1)), q, qinv), q, qinv);
-        }
-      }
-#pragma unroll
-      for (int m = 0; m < 16; ++m) sm[lds_row(rl, 16 * lh + m)] = x[m];
-    }
-    __syncthreads();
-    {
-#pragma unroll
-      for (int m = 0; m < 16; ++m) x[m] = sm[lds_row(rl, lh + 16 * m)];
-#pragma unroll
-      for (int s1 = 3; s1 >= 0; --s1) {
-        const int half = 8 >> s1;
-        const double f = F[r * 8 + s1];
-#pragma unroll
-        for (int m = 0; m < 16; ++m) {
-          if (m & half) continue;
-          gs_bfly(x[m], x[m + half], twb(T, f, s1, m >> (4 - s1), q, qinv), q, qinv);
-        }
-      }
-      double* out = it.u + ((size_t)h * np + t) * n + (size_t)r * 256;
-#pragma unroll
-      for (int m = 0; m < 16; ++m) out[lh + 16 * m] = x[m];
-    }
-    __syncthreads();  // the second polynomial reuses the LDS rows
-  }
+  for (int j = 0; j < 16; ++j) sm[lds_row(j, threadIdx.x)] = reduce(y1[j], q, qinv);
+  __syncthreads();
+  inv_b_rows(sm, out + (size_t)np * n, tile * 16, T, F, q, qinv);
 }
 
 // ---------------------------------------------------------------------------
@@ -1430,8 +1477,6 @@ __global__ __launch_bounds__(256) void k_add_limbs(double* __restrict__ dst, con
 }
 
 // --- the membership path: rescale, ct x ct tensor, constants -------------
-// Rescale, lift: lift[h][t][k] = the centred value of last[h][k] (residues of
-// the last prime, coefficient form, canonical) reduced mod q_t, t < L-1.
 #define FA_MAXLIMB 16
 struct ResArgs {
   double c[FA_MAXLIMB];   // per limb: q_last^-1 mod q_t (rescale) or a constant mod q_t
@@ -1456,27 +1501,25 @@ struct LinArgs {
   double c0[FA_MAXLIMB];
   int nterm, accumulate;
 };
-__global__ __launch_bounds__(256) void k_rescale_lift(const double* __restrict__ last, double* __restrict__ lift,
-                                                      const DevPrime* __restrict__ pr, int logn, int Lm1,
-                                                      double ql) {
-  const int n = 1 << logn;
-  const int k = blockIdx.x * 256 + threadIdx.x;
-  const int t = blockIdx.y, h = blockIdx.z;
+// Rescale, second pass: out[h][t] = (c[h][t] - lift^[h][t]) * q_last^-1 (NTT form),
+// t < L-1, with lift's row pass finished here; c has L limbs per polynomial
+struct RescaleSt {
+  const double* ct;
+  double* out;
+  double q, qinv, c, cp;
+  __device__ void operator()(size_t i, double x) const { out[i] = canon_full(mulc(ct[i] - x, c, cp, q), q, qinv); }
+};
+__global__ __launch_bounds__(256) void k_rescale_b(const double* __restrict__ ct, double* lift,
+                                                   double* __restrict__ out, ResArgs a,
+                                                   const DevPrime* __restrict__ pr, const double* __restrict__ twt,
+                                                   const double* __restrict__ twr, int logn, int L) {
+  __shared__ double sm[16 * ROWW];
+  const int n = 1 << logn, H = 1 << (logn - 8), t = blockIdx.y;
+  const size_t h = blockIdx.z;
   const double q = pr[t].q, qinv = pr[t].qinv;
-  double v = last[(size_t)h * n + k];
-  if (v > 0.5 * (ql - 1.0)) v -= ql;  // centred, |v| < q_last / 2, exact
-  lift[((size_t)h * Lm1 + t) * n + k] = canon_full(v, q, qinv);
-}
-// out[h][t] = (c[h][t] - lift^[h][t]) * q_last^-1  (NTT form), t < L-1; c has L limbs per poly
-__global__ __launch_bounds__(256) void k_rescale_combine(const double* __restrict__ ct, const double* __restrict__ lift,
-                                                         double* __restrict__ out, ResArgs a,
-                                                         const DevPrime* __restrict__ pr, int logn, int L) {
-  const int n = 1 << logn;
-  const int k = blockIdx.x * 256 + threadIdx.x;
-  const int t = blockIdx.y, h = blockIdx.z;
-  const double q = pr[t].q, qinv = pr[t].qinv;
-  const double x = ct[((size_t)h * L + t) * n + k] - lift[((size_t)h * (L - 1) + t) * n + k];
-  out[((size_t)h * (L - 1) + t) * n + k] = canon_full(mulc(x, a.c[t], a.cp[t], q), q, qinv);
+  const size_t o = (h * (L - 1) + t) * n;
+  fwd_b_body(lift + o, RescaleSt{ct + (h * L + t) * n, out + o, q, qinv, a.c[t], a.cp[t]}, twt + (size_t)t * 256,
+             twr + (size_t)t * H * 8, q, qinv, logn, sm);
 }
 // out = (x0 y0, x0 y1 + x1 y0, x1 y1) over the L primes (NTT form)
 // ciphertext j = blockIdx.z: x_j = x + j*sx with xL limbs per polynomial (its first L
@@ -1730,25 +1773,24 @@ void ntt_inv_strided(const fa_ctx* c, double* base, size_t stride, int count, in
   strided(c, base, stride, count, period, prime_off, s, false);
 }
 
-// target groups of a fused ModUp launch: a launch of at least 256 workgroups
-// keeps one group per digit (the repeated inverse passes of more groups cost
-// more than they gain there); a smaller one (one ciphertext) is split to about
-// FA_MU_WGS (default 512) workgroups, at most one group per target
-static int modup_groups(int wgs, int targets) {
-  static const int want = [] {
-    const char* e = getenv("FA_MU_WGS");
-    return e && atoi(e) > 0 ? atoi(e) : 512;
-  }();
+// Target groups of a fused conversion launch: a launch of at least 256 workgroups
+// (one per CU) keeps one group per source, as the repeated inverse passes of more
+// cost more than they gain; a smaller one (one ciphertext) is split to about 256,
+// at most one group per target.  Two workgroups fit a CU, but splitting to 512
+// measured slower (rank reduction 2.22 against 2.19 ms, the face scan 6.41 against
+// 6.26, one product at N=2^16 163 against 156 us, the fine level 817 against 788);
+// 128 was between.
+static int conv_groups(int wgs, int targets) {
   if (wgs >= 256) return 1;
-  const int g = (want + wgs - 1) / wgs;
-  return g < 1 ? 1 : g > targets ? targets : g;
+  const int g = (256 + wgs - 1) / wgs;
+  return g > targets ? targets : g;
 }
 template <int SA, int ALPHA>
 static void launch_modup_fused(const fa_ctx* c, const MuArgs& a, int count, hipStream_t s) {
   using P = PassA<SA>;
-  const int ngrp = modup_groups(c->n / P::TILE * c->dnum * count, c->np - ALPHA);
+  const int ngrp = conv_groups(c->n / P::TILE * c->dnum * count, c->np - ALPHA);
   dim3 g(c->n / P::TILE, c->dnum * ngrp, count);
-  hipLaunchKernelGGL((k_modup_fused<SA, ALPHA>), g, dim3(256), 0, s, a, c->d_pr, c->d_twa_fwd, c->d_twa_inv,
+  hipLaunchKernelGGL((k_modup_fused<SA, ALPHA>), g, dim3(512), 0, s, a, c->d_pr, c->d_twa_fwd, c->d_twa_inv,
                      c->d_mu_hat, c->d_mu_scale, c->logn, c->L, c->np, ngrp);
 }
 template <int SA>
@@ -1803,9 +1845,9 @@ static void modup_pass_b(const fa_ctx* c, const MuItem* items, int count, hipStr
 template <int SA, int KP>
 static void launch_moddown_fused(const fa_ctx* c, const MdArgs& a, int count, hipStream_t s) {
   using P = PassA<SA>;
-  const int ngrp = modup_groups(c->n / P::TILE * count, c->L);
+  const int ngrp = conv_groups(c->n / P::TILE * count, c->L);
   dim3 g(c->n / P::TILE, ngrp, count);
-  hipLaunchKernelGGL((k_moddown_fused<SA, KP>), g, dim3(256), 0, s, a, c->d_pr, c->d_twa_fwd, c->d_twa_inv,
+  hipLaunchKernelGGL((k_moddown_fused<SA, KP>), g, dim3(512), 0, s, a, c->d_pr, c->d_twa_fwd, c->d_twa_inv,
                      c->d_md_hat, c->d_md_scale, c->logn, c->L, ngrp);
 }
 template <int SA>
@@ -1918,9 +1960,13 @@ void ks_inner(const fa_ctx* c, const KsItem* items, int count, bool accumulate, 
 template <int DNUM>
 static void launch_ks_inv_b(const fa_ctx* c, const KsArgs& a, int m, hipStream_t s, int nq) {
   const int ngroup = m / nq;
-  dim3 g(ks_grid((c->n >> 8) / 16, c->K, nq, ngroup));
-  hipLaunchKernelGGL(k_ks_inv_b<DNUM>, g, dim3(256), 0, s, a, c->d_pr, c->d_twt_inv, c->d_twr_inv, c->logn, c->L,
-                     c->np, nq, ngroup);
+  dim3 g(ks_grid(c->n >> 12, c->K, nq, ngroup));
+  if (nq == 1)
+    hipLaunchKernelGGL((k_ks_inv_b<DNUM, true>), g, dim3(256), 0, s, a, c->d_pr, c->d_twt_inv, c->d_twr_inv, c->logn,
+                       c->L, c->np, nq, ngroup);
+  else
+    hipLaunchKernelGGL((k_ks_inv_b<DNUM, false>), g, dim3(256), 0, s, a, c->d_pr, c->d_twt_inv, c->d_twr_inv, c->logn,
+                       c->L, c->np, nq, ngroup);
 }
 
 void ks_inv_b(const fa_ctx* c, const KsItem* items, int count, hipStream_t s, int nq) {
@@ -2158,13 +2204,25 @@ static ResArgs res_args(const fa_ctx* c, const uint64_t* cres, int L) {
   return a;
 }
 
+template <int SA>
+static void launch_rescale_fused(const fa_ctx* c, const double* last, double* lift, int n_polys, hipStream_t s) {
+  using P = PassA<SA>;
+  const int ngrp = conv_groups(c->n / P::TILE * n_polys, c->L - 1);
+  hipLaunchKernelGGL(k_rescale_fused<SA>, dim3(c->n / P::TILE, ngrp, n_polys), dim3(512), 0, s, last, lift, c->d_pr,
+                     c->d_twa_fwd, c->d_twa_inv, c->L, ngrp);
+}
+
+// The last limb's inverse, its centred lift and the forward transform to the
+// other primes share their passes as in ModDown: three launches (a row pass, the
+// columns of both transforms with the lift between, a row pass that also
+// combines) for six.
 void rescale(const fa_ctx* c, const double* ct, int n_polys, double* out, double* scratch, hipStream_t s) {
   const size_t n = c->n;
   const int L = c->L;
   double* last = scratch;                        // [n_polys][N]
   double* lift = scratch + (size_t)n_polys * n;  // [n_polys][L-1][N]
   {
-    LimbBatch inv(c, s, false);
+    LimbBatch inv(c, s, false, !small_ring(c));
     for (int h = 0; h < n_polys; ++h) inv.add(last + (size_t)h * n, L - 1, ct + ((size_t)h * L + L - 1) * n);
   }
   std::vector<uint64_t> inv(L - 1);
@@ -2184,12 +2242,9 @@ void rescale(const fa_ctx* c, const double* ct, int n_polys, double* out, double
     for (int t = 0; t < L - 1; ++t) r.c[t] = (double)inv[t];
     return sr_rescale(c, ct, last, n_polys, out, r, s);
   }
-  const double ql = (double)c->primes[L - 1];
-  hipLaunchKernelGGL(k_rescale_lift, dim3(c->n / 256, L - 1, n_polys), dim3(256), 0, s, last, lift, c->d_pr, c->logn,
-                     L - 1, ql);
-  ntt_fwd_strided(c, lift, n, n_polys * (L - 1), L - 1, 0, s);
-  hipLaunchKernelGGL(k_rescale_combine, dim3(c->n / 256, L - 1, n_polys), dim3(256), 0, s, ct, lift, out,
-                     res_args(c, inv.data(), L - 1), c->d_pr, c->logn, L);
+  FA_SA_SWITCH(launch_rescale_fused, c, last, lift, n_polys, s)
+  hipLaunchKernelGGL(k_rescale_b, dim3((c->n >> 8) / 16, L - 1, n_polys), dim3(256), 0, s, ct, lift, out,
+                     res_args(c, inv.data(), L - 1), c->d_pr, c->d_twt_fwd, c->d_twr_fwd, c->logn, L);
 }
 
 void tensor(const fa_ctx* c, const double* x, int xL, size_t sx, const double* y, int yL, size_t sy, int count,

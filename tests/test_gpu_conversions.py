@@ -1,0 +1,50 @@
+"""The fused basis conversions of rings from N = 2^14 (ModUp, ModDown and rescale: the column pass
+of the inverse transform, the conversion and the first forward pass in one kernel): every column
+height, every digit width, short last digits, and launches with the targets in one and in several
+groups, each against the oracle word for word."""
+import numpy as np
+import pytest
+
+import common
+from common import Pair, say
+from oracle import ckks
+from paper_2608_21131_amd import gen
+
+pytestmark = pytest.mark.gpu
+
+SETS = [(14, 3, 1), (14, 5, 2), (14, 2, 3), (15, 4, 3), (15, 3, 4), (15, 2, 1), (16, 2, 1), (16, 3, 2), (16, 5, 4)]
+common.PARAMS.update({f"c{logn}_{L}_{K}": (logn, L, K) for logn, L, K in SETS})
+
+
+# one ciphertext: the targets split into groups; three or five: fewer groups, then one
+@pytest.mark.parametrize("logn,L,K,count", [(*s, c) for s in SETS for c in (1, 3)] + [(14, 5, 2, 17), (15, 4, 3, 5)])
+def test_rotation_sums(logn, L, K, count):
+    p = Pair(f"c{logn}_{L}_{K}", wid=70)
+    g = np.random.default_rng(logn + L)
+    keys = p.keys([3])
+    both = [p.encrypt_both(ckks.encode(g.uniform(-1, 1, p.par.slots), p.n, 40), tag=j) for j in range(count)]
+    cts = p.ctx.new_ct(count, log_scale=40)
+    for j, (dev, _) in enumerate(both):
+        cts.t[j * p.ctx.ct_words:(j + 1) * p.ctx.ct_words] = dev.t
+    say(f"[conv] N=2^{logn} {L}+{K} primes, {count} ciphertexts")
+    p.ctx.rotate_sum(cts, None, 3, 1)
+    got = p.export_ct(cts, count)
+    for j in {0, count - 1}:
+        assert np.array_equal(got[j], p.orc.rotate_sum(both[j][1], 3, 1, keys)), j
+
+
+@pytest.mark.parametrize("logn,L", [(11, 2), (13, 4), (14, 2), (14, 6), (15, 5), (16, 2), (16, 4)])
+@pytest.mark.parametrize("n_polys", [1, 2, 3])
+def test_rescale(logn, L, n_polys):
+    from paper_2608_21131_amd import fa
+    par = ckks.Params(logn=logn, L=L, K=1)
+    hi = fa.Context(logn, L, 1, 40)
+    lo = hi.at_level(L - 1)
+    x = np.stack([gen.uniform_residues(gen.rng(71, gen.STREAM_ENC_A, h), par.q, 1, par.n)[0] for h in range(n_polys)])
+    # the rounding's edges: the last residue 0, either side of half its prime, and its largest
+    last = par.q[-1]
+    x[:, -1, :4] = [0, (last - 1) // 2, (last + 1) // 2, last - 1]
+    say(f"[rescale] N=2^{logn} {L} primes, {n_polys} polynomials")
+    buf = hi.import_coeffs(x, n_polys=n_polys)
+    got = lo.export(hi.rescale(lo, buf, n_polys=n_polys)).reshape(n_polys, L - 1, par.n)
+    assert np.array_equal(got, ckks.Oracle(par).rescale(x))
