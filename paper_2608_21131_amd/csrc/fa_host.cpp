@@ -1770,7 +1770,8 @@ static int giant_phase(fa_ctx* c, const double* acc, int nb, int G, int B, doubl
       }
     }
     if ((rc = join_lanes(c, s, gl))) return rc;
-    fa::giant_ks(c, gext, accb, astride, keys.data(), ggal.data(), cb, G - 1, usum, s);
+    // the ModUps' row-passed c1 is read out by now: scratch for split giants
+    fa::giant_ks(c, gext, accb, astride, keys.data(), ggal.data(), cb, G - 1, usum, gy, lanes * gy_l, s);
     std::vector<const double*> bases(2 * cb);
     std::vector<double*> douts(2 * cb);
     std::vector<uint32_t> gals(2 * cb, 1u);

@@ -202,8 +202,10 @@ void ks_inv_b(const fa_ctx* c, const KsItem* items, int count, hipStream_t s, in
 // Fused giant steps of nb blocks: u[blk] = sum_{g=1..ng} sum_i sigma_g(NTT(ext)_i) key_g[i]
 // + P sigma_g(acc_g.c0), with ext = [nb][ng][dnum][np][N] holding only the first
 // forward pass of the extended digits of acc_g.c1 (acc_g = acc + blk*astride + g*2LN).
+// part: part_words words of scratch for the sums of split giants (fewer, or none,
+// only keep a small launch from being split).
 void giant_ks(const fa_ctx* c, const double* ext, const double* acc, size_t astride, const double* const* keys,
-              const uint32_t* gals, int nb, int ng, double* u, hipStream_t s);
+              const uint32_t* gals, int nb, int ng, double* u, double* part, size_t part_words, hipStream_t s);
 
 
 // For each query j < nq: acc[j][blk][g][2][L][N] = sum_b pts[blk][(g*B+b)][L][N] * rot_b[2][L][N]

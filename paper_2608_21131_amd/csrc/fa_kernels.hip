@@ -943,6 +943,13 @@ __global__ __launch_bounds__(256) void k_ks_inv_b(KsArgs args, const DevPrime* _
 // NTT form never reach HBM.  The digit's own limbs come from acc_g.c1 itself.
 // Workgroup ids are decoded so that the nb blocks of one (tile, prime) land on
 // the same XCD one after the other and share the key rows in its L2.
+//
+// A workgroup is a serial chain of giants times digits, each a load, two halves
+// of a row pass and a gather with barriers between: 7.5 us apiece whatever else
+// runs.  Where the (tile, prime, block) triples leave the chip's 512 places (two
+// workgroups a CU) more than half empty, the giants are split into groups with
+// sums of their own, added by k_sum_parts: one block at N = 2^16 and 12+3 primes
+// (240 triples, 7 giants) took 210 us in one group.
 // ---------------------------------------------------------------------------
 #define FA_MAXG 32
 struct GiantArgs {
@@ -951,8 +958,10 @@ struct GiantArgs {
   const double* key[FA_MAXG];
   uint32_t gal[FA_MAXG];
   double* u;          // [nb][2][np][N]
+  double* part;       // sums of the giant groups after the first, each as u
   size_t astride;
   int nb, ng, ngs, g0, accumulate;  // ng giants in this launch; ngs: the giant stride of ext
+  int per;                          // giants per group (blockIdx.y)
 };
 
 template <int DNUM, int ROWS>
@@ -977,8 +986,9 @@ __global__ __launch_bounds__(256) void k_giant_ks(GiantArgs a, const DevPrime* _
   double acc0[ROWS], acc1[ROWS];
 #pragma unroll
   for (int j = 0; j < ROWS; ++j) acc0[j] = acc1[j] = 0.0;
+  const int glo = (int)blockIdx.y * a.per, ghi = min(a.ng, glo + a.per);
 #pragma unroll 1
-  for (int g = 0; g < a.ng; ++g) {
+  for (int g = glo; g < ghi; ++g) {
     const uint32_t gal = a.gal[g];
     const uint32_t sbase = perm(k0, gal, logn) & ~(TW - 1u);
     const double* __restrict__ accg = a.acc + (size_t)blk * a.astride + (size_t)(a.g0 + g) * 2 * ln;
@@ -1025,7 +1035,8 @@ __global__ __launch_bounds__(256) void k_giant_ks(GiantArgs a, const DevPrime* _
       acc1[j] = reduce(acc1[j], q, qinv);
     }
   }
-  double* u0 = a.u + ((size_t)blk * 2 * np + t) * n + k0 + threadIdx.x;
+  double* u = blockIdx.y ? a.part + (size_t)(blockIdx.y - 1) * a.nb * 2 * np * n : a.u;
+  double* u0 = u + ((size_t)blk * 2 * np + t) * n + k0 + threadIdx.x;
   double* u1 = u0 + (size_t)np * n;
 #pragma unroll
   for (int j = 0; j < ROWS; ++j) {
@@ -1037,6 +1048,17 @@ __global__ __launch_bounds__(256) void k_giant_ks(GiantArgs a, const DevPrime* _
     u0[256 * j] = canon_full(r0, q, qinv);
     u1[256 * j] = canon_full(r1, q, qinv);
   }
+}
+
+// u += the parts parts of `words` words each, canonical (limb r over prime r % np)
+__global__ __launch_bounds__(256) void k_sum_parts(double* __restrict__ u, const double* __restrict__ part, int parts,
+                                                   const DevPrime* __restrict__ pr, int logn, int np) {
+  const size_t o = ((size_t)blockIdx.y << logn) + blockIdx.x * 256 + threadIdx.x;
+  const size_t words = (size_t)gridDim.y << logn;
+  const int t = blockIdx.y % np;
+  double v = u[o];
+  for (int i = 0; i < parts; ++i) v += part[i * words + o];  // at most 7 parts: below 8q
+  u[o] = canon_full(v, pr[t].q, pr[t].qinv);
 }
 
 // ---------------------------------------------------------------------------
@@ -1984,16 +2006,28 @@ void ks_inv_b(const fa_ctx* c, const KsItem* items, int count, hipStream_t s, in
 }
 
 template <int DNUM>
-static void launch_giant(const fa_ctx* c, const GiantArgs& a, hipStream_t s) {
+static void launch_giant(const fa_ctx* c, const GiantArgs& a, int groups, hipStream_t s) {
   const int ntile = (c->n >> 8) / 16;
   const int rest8 = (ntile * c->np + 7) / 8;
-  dim3 g((unsigned)(8 * a.nb * rest8));
+  dim3 g((unsigned)(8 * a.nb * rest8), groups);
   hipLaunchKernelGGL((k_giant_ks<DNUM, 16>), g, dim3(256), 0, s, a, c->d_pr, c->d_twt_fwd, c->d_twr_fwd, c->logn,
                      c->L, c->np, c->alpha, ntile);
 }
 
+// Groups the giants of one launch are split into (see k_giant_ks): as many as
+// keep the launch within the chip's 512 places, no more than there are giants,
+// than the scratch holds or than k_sum_parts adds.
+static int giant_groups(const fa_ctx* c, int nb, int ng, size_t part_words) {
+  const long places = 512, wgs = (long)(c->n >> 12) * c->np * nb;
+  const size_t one = (size_t)nb * 2 * c->np * c->n;
+  long g = places / wgs;
+  if (g > 1 + (long)(part_words / one)) g = 1 + (long)(part_words / one);
+  if (g > ng) g = ng;
+  return g < 1 ? 1 : g > 8 ? 8 : (int)g;
+}
+
 void giant_ks(const fa_ctx* c, const double* ext, const double* acc, size_t astride, const double* const* keys,
-              const uint32_t* gals, int nb, int ng, double* u, hipStream_t s) {
+              const uint32_t* gals, int nb, int ng, double* u, double* part, size_t part_words, hipStream_t s) {
   const size_t ext_g = (size_t)c->dnum * c->np * c->n;
   for (int g0 = 0; g0 < ng; g0 += FA_MAXG) {
     GiantArgs a;
@@ -2006,23 +2040,30 @@ void giant_ks(const fa_ctx* c, const double* ext, const double* acc, size_t astr
       a.gal[g] = gals[g0 + g];
     }
     a.u = u;
+    a.part = part;
     a.astride = astride;
     a.nb = nb;
     a.ng = m;
     a.ngs = ng;
     a.g0 = 1 + g0;
     a.accumulate = g0 > 0;
+    // a later chunk adds to u, so only a single one is split
+    a.per = ng > FA_MAXG ? m : (m + giant_groups(c, nb, m, part_words) - 1) / giant_groups(c, nb, m, part_words);
+    const int groups = (m + a.per - 1) / a.per;
     switch (c->dnum) {
-      case 1: launch_giant<1>(c, a, s); break;
-      case 2: launch_giant<2>(c, a, s); break;
-      case 3: launch_giant<3>(c, a, s); break;
-      case 4: launch_giant<4>(c, a, s); break;
-      case 5: launch_giant<5>(c, a, s); break;
-      case 6: launch_giant<6>(c, a, s); break;
-      case 7: launch_giant<7>(c, a, s); break;
-      case 8: launch_giant<8>(c, a, s); break;
+      case 1: launch_giant<1>(c, a, groups, s); break;
+      case 2: launch_giant<2>(c, a, groups, s); break;
+      case 3: launch_giant<3>(c, a, groups, s); break;
+      case 4: launch_giant<4>(c, a, groups, s); break;
+      case 5: launch_giant<5>(c, a, groups, s); break;
+      case 6: launch_giant<6>(c, a, groups, s); break;
+      case 7: launch_giant<7>(c, a, groups, s); break;
+      case 8: launch_giant<8>(c, a, groups, s); break;
       default: break;
     }
+    if (groups > 1)
+      hipLaunchKernelGGL(k_sum_parts, dim3(c->n / 256, nb * 2 * c->np), dim3(256), 0, s, u, part, groups - 1, c->d_pr,
+                         c->logn, c->np);
   }
 }
 

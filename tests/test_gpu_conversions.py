@@ -48,3 +48,21 @@ def test_rescale(logn, L, n_polys):
     buf = hi.import_coeffs(x, n_polys=n_polys)
     got = lo.export(hi.rescale(lo, buf, n_polys=n_polys)).reshape(n_polys, L - 1, par.n)
     assert np.array_equal(got, ckks.Oracle(par).rescale(x))
+
+
+# giant sums split into groups: 7 giants in up to 7 groups, 5 in uneven ones, one alone, and 63 (two
+# launches, the second adding to the first: not split); from 6 blocks on fewer groups
+@pytest.mark.parametrize("logn,L,K,d,B,blocks", [(14, 3, 1, 16, 2, 1), (14, 5, 2, 64, 1, 1), (15, 3, 4, 32, 4, 2),
+                                                 (16, 2, 1, 8, 4, 1), (14, 5, 2, 16, 2, 6), (14, 2, 3, 8, 1, 9)])
+def test_split_giant_sums(logn, L, K, d, B, blocks):
+    p = Pair(f"c{logn}_{L}_{K}", wid=72)
+    g = np.random.default_rng(d + blocks)
+    keys = p.keys(ckks.steps_for_bsgs(d, B))
+    ct_dev, ct_orc = p.encrypt_both(ckks.encode(g.uniform(-1, 1, p.par.slots), p.n, 40))
+    coeffs = g.integers(-2 ** 30, 2 ** 30, (blocks, d, p.n))
+    say(f"[giant] N=2^{logn} {L}+{K} primes d={d} B={B} blocks={blocks}")
+    got = p.export_ct(p.ctx.score_block(ct_dev, [p.ctx.encode_db_block_int(c) for c in coeffs], d, 1, B), blocks)
+    rots = p.orc.baby_rotations(ct_orc, B, keys)
+    for j in {0, blocks - 1}:
+        pts = np.stack([ckks.to_residues(c, p.par.q) for c in coeffs[j]]).reshape(d // B, B, p.par.L, p.n)
+        assert np.array_equal(got[j], p.orc.bsgs_block(rots, pts, B, d // B, keys)), j
