@@ -121,9 +121,10 @@ namespace fa {
 void encode_slots(const fa_ctx* c, const EncArgs& a, int p0, int count, double* z, size_t zst, int64_t* out,
                   double scale, hipStream_t s) {
   const int tiles = c->n > kTile ? c->n / kTile : 1;
-  const double2* root = reinterpret_cast<const double2*>(c->d_fft_root);
-  const double2* twist = reinterpret_cast<const double2*>(c->d_fft_twist);
-  hipLaunchKernelGGL(k_enc_a, dim3(tiles, count), dim3(256), 0, s, Rows{a, c->n / 2}, p0, z, zst, root, c->d_fft_slot,
+  const double2* root = reinterpret_cast<const double2*>(c->d_fft);
+  const double2* twist = root + c->n / 2;
+  const uint32_t* slot = reinterpret_cast<const uint32_t*>(twist + c->n);
+  hipLaunchKernelGGL(k_enc_a, dim3(tiles, count), dim3(256), 0, s, Rows{a, c->n / 2}, p0, z, zst, root, slot,
                      c->logn);
   hipLaunchKernelGGL(k_enc_b, dim3(tiles, count), dim3(256), 0, s, z, zst, out, root, twist, c->logn, scale);
 }

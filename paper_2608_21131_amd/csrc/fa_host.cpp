@@ -154,12 +154,44 @@ static uint32_t galois(int n, long step) {
 namespace {
 using cplx = std::complex<double>;
 
+// Place of point i in the transforms' arrays: 64 bytes of padding per 4 KiB, as the
+// points of one butterfly are powers of two apart and would share a cache set.
+constexpr int kRun = 512;
+constexpr size_t fft_at(size_t i) { return i + (i / kRun) * 8; }
+// The two parts of n points in one allocation, their own distance off a power of two
+struct FftBuf {
+  std::unique_ptr<double[]> mem;
+  double *re, *im;
+  explicit FftBuf(int n) : mem(new double[2 * fft_at(n) + 32]), re(mem.get()), im(re + fft_at(n) + 32) {}
+};
+
+// Per-stage twiddles of a radix-2 transform of length n one after the other: for
+// the stage of span len (len = 4, 8, ..., n) e^{sign 2 pi i j / len}, j < len/2, at
+// offset len/2 - 2, taken from one length-n table (index j n / len) so that every
+// stage uses the same rounded values.  The span-2 stage needs none.
+struct StageTwiddles {
+  std::vector<double> re, im;
+  void fill(int n, const cplx* root) {
+    re.assign(n > 2 ? n - 2 : 0, 0.0);
+    im = re;
+    for (int len = 4; len <= n; len <<= 1)
+      for (int j = 0; j < len / 2; ++j) {
+        const cplx w = root[(size_t)j * (n / len)];
+        re[len / 2 - 2 + j] = w.real();
+        im[len / 2 - 2 + j] = w.imag();
+      }
+  }
+};
+
 // Tables of the host transforms for ring degree n, built once per n and
 // shared by every context (they depend on n only).
 struct FftTables {
-  std::vector<cplx> root_fwd, root_inv;  // e^{-2 pi i k / n}, e^{+2 pi i k / n}, k < n/2
+  std::vector<cplx> root_fwd;            // e^{-2 pi i k / n}, k < n/2
   std::vector<cplx> twist;               // e^{i pi k / n}, k < n
   std::vector<u64> e;                    // slot exponents 5^j mod 2n, j < n/2
+  StageTwiddles stage;                   // of root_fwd
+  std::vector<uint32_t> pos, pos_conj;   // places of slot j's points (e_j - 1)/2, (2n - e_j - 1)/2
+  std::vector<char> device;              // image of the GPU's tables (ensure_fft): root_fwd, twist, point -> slot
 };
 const FftTables& fft_tables(int n) {
   static std::mutex mu;
@@ -169,67 +201,157 @@ const FftTables& fft_tables(int n) {
   if (!slot) {
     auto t = std::make_unique<FftTables>();
     t->root_fwd.resize(n / 2);
-    t->root_inv.resize(n / 2);
     for (int k = 0; k < n / 2; ++k) {
       const double ang = 2.0 * M_PI * (double)k / (double)n;
       t->root_fwd[k] = cplx(std::cos(ang), -std::sin(ang));
-      t->root_inv[k] = cplx(std::cos(ang), std::sin(ang));
     }
+    t->stage.fill(n, t->root_fwd.data());
     t->twist.resize(n);
     for (int k = 0; k < n; ++k) {
       const double ang = M_PI * (double)k / (double)n;
       t->twist[k] = cplx(std::cos(ang), std::sin(ang));
     }
+    int bits = 0;
+    while ((1 << bits) < n) ++bits;
     t->e.resize(n / 2);
+    t->pos.resize(n / 2);
+    t->pos_conj.resize(n / 2);
     u64 x = 1;
     for (int j = 0; j < n / 2; ++j) {
       t->e[j] = x;
+      t->pos[j] = (uint32_t)fft_at(bitrev((uint32_t)((x - 1) / 2), bits));
+      t->pos_conj[j] = (uint32_t)fft_at(bitrev((uint32_t)((2ull * n - x - 1) / 2), bits));
       x = x * 5 % (2ull * n);
     }
+    t->device.resize((size_t)n * 28);
+    std::memcpy(t->device.data(), t->root_fwd.data(), (size_t)n * 8);
+    std::memcpy(t->device.data() + (size_t)n * 8, t->twist.data(), (size_t)n * 16);
+    uint32_t* ds = reinterpret_cast<uint32_t*>(t->device.data() + (size_t)n * 24);
+    for (int j = 0; j < n / 2; ++j) ds[(t->e[j] - 1) / 2] = ds[(2ull * n - t->e[j] - 1) / 2] = (uint32_t)j;
     slot = std::move(t);
   }
   return *slot;
 }
 
-// in-place radix-2 FFT of length n with the root table of the wanted sign
-// (root_fwd: sum x_t e^{-2 pi i k t / n}; root_inv: e^{+...})
-void fft(std::vector<cplx>& a, const std::vector<cplx>& root) {
-  const size_t n = a.size();
-  for (size_t i = 1, j = 0; i < n; ++i) {
-    size_t bit = n >> 1;
-    for (; j & bit; bit >>= 1) j ^= bit;
-    j ^= bit;
-    if (i < j) std::swap(a[i], a[j]);
+// The stages of span len0 .. n of a radix-2 transform in place over split real /
+// imaginary arrays in bit-reversed order, two stages a pass over memory (each
+// butterfly as in a pass of its own: u + v w and u - v w, the product as two
+// products and their difference or sum).
+__attribute__((always_inline)) inline void fft_stages_body(double* re, double* im, int n, int len0,
+                                                           const StageTwiddles& tw) {
+  int len = len0;
+  int stages = 0;
+  for (int l = len0; l <= n; l <<= 1) ++stages;
+  if (stages & 1) {  // the shortest one alone: len0 <= kRun
+    const int h = len / 2;
+    const double *wr = tw.re.data() + (h - 2), *wi = tw.im.data() + (h - 2);
+    for (int s0 = 0; s0 < n; s0 += len) {
+      double *ar = re + fft_at(s0), *ai = im + fft_at(s0), *br = ar + h, *bi = ai + h;
+      for (int j = 0; j < h; ++j) {
+        const double vr = br[j] * wr[j] - bi[j] * wi[j];
+        const double vi = br[j] * wi[j] + bi[j] * wr[j];
+        const double ur = ar[j], ui = ai[j];
+        ar[j] = ur + vr;
+        ai[j] = ui + vi;
+        br[j] = ur - vr;
+        bi[j] = ui - vi;
+      }
+    }
+    len <<= 1;
   }
-  for (size_t len = 2; len <= n; len <<= 1) {
-    const size_t step = n / len;
-    for (size_t s = 0; s < n; s += len)
-      for (size_t j = 0; j < len / 2; ++j) {
-        const cplx u = a[s + j], v = a[s + j + len / 2] * root[j * step];
-        a[s + j] = u + v;
-        a[s + j + len / 2] = u - v;
+  for (; len <= n; len <<= 2) {
+    const int h = len / 2, run = h < kRun ? h : kRun;
+    for (int s0 = 0; s0 < n; s0 += 2 * len)
+      for (int j0 = 0; j0 < h; j0 += run) {
+        const double *w1r = tw.re.data() + (h - 2) + j0, *w1i = tw.im.data() + (h - 2) + j0;
+        const double *w2r = tw.re.data() + (len - 2) + j0, *w2i = tw.im.data() + (len - 2) + j0;
+        const double *w3r = w2r + h, *w3i = w2i + h;
+        const size_t p0 = fft_at(s0 + j0), p1 = fft_at(s0 + j0 + h), p2 = fft_at(s0 + j0 + 2 * h),
+                     p3 = fft_at(s0 + j0 + 3 * h);
+        double *r0 = re + p0, *r1 = re + p1, *r2 = re + p2, *r3 = re + p3;
+        double *i0 = im + p0, *i1 = im + p1, *i2 = im + p2, *i3 = im + p3;
+        // the eight runs and the tables are disjoint
+#pragma clang loop vectorize(assume_safety)
+        for (int j = 0; j < run; ++j) {
+          const double v1r = r1[j] * w1r[j] - i1[j] * w1i[j], v1i = r1[j] * w1i[j] + i1[j] * w1r[j];
+          const double v3r = r3[j] * w1r[j] - i3[j] * w1i[j], v3i = r3[j] * w1i[j] + i3[j] * w1r[j];
+          const double a0r = r0[j] + v1r, a0i = i0[j] + v1i, a1r = r0[j] - v1r, a1i = i0[j] - v1i;
+          const double a2r = r2[j] + v3r, a2i = i2[j] + v3i, a3r = r2[j] - v3r, a3i = i2[j] - v3i;
+          const double u2r = a2r * w2r[j] - a2i * w2i[j], u2i = a2r * w2i[j] + a2i * w2r[j];
+          const double u3r = a3r * w3r[j] - a3i * w3i[j], u3i = a3r * w3i[j] + a3i * w3r[j];
+          r0[j] = a0r + u2r;
+          i0[j] = a0i + u2i;
+          r2[j] = a0r - u2r;
+          i2[j] = a0i - u2i;
+          r1[j] = a1r + u3r;
+          i1[j] = a1i + u3i;
+          r3[j] = a1r - u3r;
+          i3[j] = a1i - u3i;
+        }
       }
   }
 }
 
-const std::vector<u64>& slot_exps(int n) { return fft_tables(n).e; }
-
 // m_k = rint(scale * (2/N) sum_j v_j cos(pi k e_j / N)) via one length-N FFT:
 // sum_j v_j (w^{-k e_j} + w^{k e_j}) = w^{-k} sum_t Z_t e^{-2 pi i k t / N},
 // w = e^{i pi / N}, Z_t = v_j at t = (e_j - 1)/2 and t = (2N - e_j - 1)/2.
-void encode_one(int n, const std::vector<u64>& e, const double* v, int nv, double scale, int64_t* out) {
-  const FftTables& tb = fft_tables(n);
-  std::vector<cplx> z(n, cplx(0, 0));
-  for (int j = 0; j < nv; ++j) {
-    z[(e[j] - 1) / 2] = v[j];
-    z[(2 * (u64)n - e[j] - 1) / 2] = v[j];
+// k_enc_a and k_enc_b (fa_encode.hip) run the same butterflies on the GPU.
+__attribute__((always_inline)) inline void encode_body(int n, const FftTables& tb, const double* v, int nv,
+                                                       double scale, int64_t* out, double* re, double* im) {
+  if (nv < n / 2) std::fill(re, re + fft_at(n), 0.0);
+  for (int j = 0; j < nv; ++j) re[tb.pos[j]] = re[tb.pos_conj[j]] = v[j];
+  // spans 2 and 4 on real input
+  const double wr = tb.stage.re[1], wi = tb.stage.im[1];
+  for (int s0 = 0; s0 < n; s0 += 4) {
+    const size_t s = fft_at(s0);
+    const double a0 = re[s] + re[s + 1], a1 = re[s] - re[s + 1], a2 = re[s + 2] + re[s + 3], a3 = re[s + 2] - re[s + 3];
+    const double vr = a3 * wr, vi = a3 * wi;
+    re[s] = a0 + a2;
+    re[s + 2] = a0 - a2;
+    re[s + 1] = a1 + vr;
+    re[s + 3] = a1 - vr;
+    im[s] = im[s + 2] = 0.0;
+    im[s + 1] = vi;
+    im[s + 3] = -vi;
   }
-  fft(z, tb.root_fwd);
+  fft_stages_body(re, im, n, 8, tb.stage);
+  const double inv_n = 1.0 / (double)n;  // a power of two: the product is the quotient
   for (int k = 0; k < n; ++k) {
     // Re(z_k w^-k), w = e^{i pi / N}
-    const double re = z[k].real() * tb.twist[k].real() + z[k].imag() * tb.twist[k].imag();
-    out[k] = (int64_t)std::nearbyint(scale * re / (double)n);
+    const size_t p = fft_at(k);
+    const double x = re[p] * tb.twist[k].real() + im[p] * tb.twist[k].imag();
+    out[k] = (int64_t)__builtin_nearbyint(scale * x * inv_n);
   }
+}
+// The same arithmetic four lanes wide, and the rounding one instruction instead
+// of a library call, where the CPU has AVX2 (no FMA: products and sums round as
+// everywhere).
+#if !defined(__HIP_DEVICE_COMPILE__) && defined(__x86_64__)
+__attribute__((target("avx2"))) void encode_avx2(int n, const FftTables& tb, const double* v, int nv, double scale,
+                                                 int64_t* out, double* re, double* im) {
+  encode_body(n, tb, v, nv, scale, out, re, im);
+}
+__attribute__((target("avx2"))) void fft_stages_avx2(double* re, double* im, int n, int len0, const StageTwiddles& tw) {
+  fft_stages_body(re, im, n, len0, tw);
+}
+bool have_avx2() {
+  static const bool v = __builtin_cpu_supports("avx2");
+  return v;
+}
+#else
+void encode_avx2(int, const FftTables&, const double*, int, double, int64_t*, double*, double*) {}
+void fft_stages_avx2(double*, double*, int, int, const StageTwiddles&) {}
+bool have_avx2() { return false; }
+#endif
+void fft_stages(double* re, double* im, int n, int len0, const StageTwiddles& tw) {
+  if (have_avx2()) fft_stages_avx2(re, im, n, len0, tw);
+  else fft_stages_body(re, im, n, len0, tw);
+}
+void encode_one(int n, const double* v, int nv, double scale, int64_t* out) {
+  const FftTables& tb = fft_tables(n);
+  FftBuf b(n);
+  if (have_avx2()) encode_avx2(n, tb, v, nv, scale, out, b.re, b.im);
+  else encode_body(n, tb, v, nv, scale, out, b.re, b.im);
 }
 }  // namespace
 
@@ -354,9 +476,7 @@ void fa_ctx_destroy(fa_ctx* c) {
   (void)hipFree(c->d_twr_inv);
   (void)hipFree(c->d_tws_fwd);
   (void)hipFree(c->d_tws_inv);
-  (void)hipFree(c->d_fft_root);
-  (void)hipFree(c->d_fft_twist);
-  (void)hipFree(c->d_fft_slot);
+  (void)hipFree(c->d_fft);
   (void)hipFree(c->d_mu_hat);
   (void)hipFree(c->d_md_hat);
   (void)hipFree(c->d_mu_scale);
@@ -746,6 +866,19 @@ int fa_keygen_relin(fa_ctx* c, const int64_t* s, const uint64_t* a, const int64_
 int fa_has_relin_key(const fa_ctx* c) { return c && c->d_rlk ? 1 : 0; }
 
 
+// The context's device staging of the client calls: at least 2 * words words at
+// c->d_export, grown on demand.  The caller holds export_mu until its work on the
+// staging is synchronised.
+static int ensure_export(fa_ctx* c, size_t words) {
+  if (c->export_words >= words) return FA_OK;
+  (void)hipFree(c->d_export);
+  c->d_export = nullptr;
+  c->export_words = 0;
+  if (int rc = dev_alloc(&c->d_export, 2 * words)) return rc;
+  c->export_words = words;
+  return FA_OK;
+}
+
 int fa_encrypt(fa_ctx* c, const int64_t* m, int32_t log_scale, const uint64_t* a, const int64_t* e, fa_buf* ct,
                void* stream) {
   if (!c || !m || !a || !e) return fail(FA_E_INVAL, "fa_encrypt: null argument");
@@ -759,15 +892,12 @@ int fa_encrypt(fa_ctx* c, const int64_t* m, int32_t log_scale, const uint64_t* a
       return fail(FA_E_INVAL, "fa_encrypt: coefficient %zu out of range", k);
   std::vector<int64_t> me(n);
   for (size_t k = 0; k < n; ++k) me[k] = m[k] + e[k];
-  uint64_t* du = nullptr;
-  int64_t* dm = nullptr;
-  double* dv = nullptr;
-  int rc;
-  if ((rc = dev_alloc(&du, L * n)) || (rc = dev_alloc(&dm, n)) || (rc = dev_alloc(&dv, L * n))) {
-    (void)hipFree(du);
-    (void)hipFree(dm);
-    return rc;
-  }
+  std::lock_guard<std::mutex> lock(c->export_mu);
+  int rc = ensure_export(c, (L + 1) * n);
+  if (rc) return rc;
+  uint64_t* du = reinterpret_cast<uint64_t*>(c->d_export);
+  int64_t* dm = reinterpret_cast<int64_t*>(du + L * n);
+  double* dv = c->d_export + (L + 1) * n;
   double* dct = (double*)ct->dev;
   HIPCHK(hipMemcpyAsync(du, a, L * n * 8, hipMemcpyHostToDevice, s));
   HIPCHK(hipMemcpyAsync(dm, me.data(), n * 8, hipMemcpyHostToDevice, s));
@@ -776,11 +906,10 @@ int fa_encrypt(fa_ctx* c, const int64_t* m, int32_t log_scale, const uint64_t* a
   fa::int_to_res(c, dm, 1, (int)L, dv, s);
   fa::ntt_fwd_strided(c, dv, n, (int)L, (int)L, 0, s);
   fa::enc_combine(c, dct, dv, s);
-  if ((rc = check_launch("fa_encrypt"))) return rc;
+  // synchronised on a failed launch too: the staging is the next caller's
+  rc = check_launch("fa_encrypt");
   HIPCHK(hipStreamSynchronize(s));
-  (void)hipFree(du);
-  (void)hipFree(dm);
-  (void)hipFree(dv);
+  if (rc) return rc;
   out_set(c, ct, 2, 1, log_scale);
   return FA_OK;
 }
@@ -841,17 +970,7 @@ static int export_polys(fa_ctx* c, const double* src, int n_polys, uint64_t* out
   const size_t n = c->n, L = c->L;
   const size_t words = (size_t)n_polys * L * n;
   std::lock_guard<std::mutex> lock(c->export_mu);
-  if (c->export_words < words) {
-    if (c->d_export) {
-      HIPCHK(hipStreamSynchronize(s));
-      (void)hipFree(c->d_export);
-      c->d_export = nullptr;
-      c->export_words = 0;
-    }
-    int rc = dev_alloc(&c->d_export, 2 * words);
-    if (rc) return rc;
-    c->export_words = words;
-  }
+  if (int rc = ensure_export(c, words)) return rc;
   double* tmp = c->d_export;
   uint64_t* du = reinterpret_cast<uint64_t*>(c->d_export + c->export_words);
   if (decrypt) {
@@ -932,8 +1051,7 @@ int fa_encode(const fa_ctx* c, const double* slots, int n_slots, int log_scale, 
   if (!c || !slots || !out) return fail(FA_E_INVAL, "fa_encode: null argument");
   if (n_slots < 0 || n_slots > c->n / 2) return fail(FA_E_SHAPE, "fa_encode: n_slots %d > N/2", n_slots);
   if (log_scale < 0 || log_scale > 61) return fail(FA_E_INVAL, "fa_encode: log_scale out of range");
-  const std::vector<u64>& e = slot_exps(c->n);
-  encode_one(c->n, e, slots, n_slots, std::ldexp(1.0, log_scale), out);
+  encode_one(c->n, slots, n_slots, std::ldexp(1.0, log_scale), out);
   return FA_OK;
 }
 
@@ -995,47 +1113,11 @@ inline double garner_to_double(const Garner& g, const uint64_t* res, size_t stri
   return x;
 }
 
-// A_t = sum_k x_k e^{+2 pi i k t / n} over split real / imaginary arrays that
-// already hold x in bit-reversed order (x_k at index brev(k)); n a power of
-// two, radix-2 stages in place, A_t at index t.  twr / twi hold the stages'
-// twiddles one after the other: for the stage of span len (len = 4, 8, ...,
-// n), e^{+2 pi i j / len} for j < len/2 at offset len/2 - 2 (see dec_tables);
-// the span-2 stage needs none.
-void fft_pos_brev_in(double* re, double* im, int n, const double* twr, const double* twi) {
-  for (int s0 = 0; s0 < n; s0 += 2) {
-    const double ur = re[s0], ui = im[s0], vr = re[s0 + 1], vi = im[s0 + 1];
-    re[s0] = ur + vr;
-    im[s0] = ui + vi;
-    re[s0 + 1] = ur - vr;
-    im[s0 + 1] = ui - vi;
-  }
-  for (int len = 4; len <= n; len <<= 1) {
-    const int h = len / 2;
-    const double* wr = twr + (h - 2);  // stage offsets: 0, 2, 6, 14, ... = h - 2
-    const double* wi = twi + (h - 2);
-    for (int s0 = 0; s0 < n; s0 += len) {
-      double* ar = re + s0;
-      double* ai = im + s0;
-      double* br = re + s0 + h;
-      double* bi = im + s0 + h;
-      for (int j = 0; j < h; ++j) {
-        const double vr = br[j] * wr[j] - bi[j] * wi[j];
-        const double vi = br[j] * wi[j] + bi[j] * wr[j];
-        const double ur = ar[j], ui = ai[j];
-        ar[j] = ur + vr;
-        ai[j] = ui + vi;
-        br[j] = ur - vr;
-        bi[j] = ui - vi;
-      }
-    }
-  }
-}
-
-// decode tables of ring degree n: e^{+2 pi i k / (n/2)} for k < n/4 (split),
-// and the slot -> transform index map t_j = (5^j mod 2n - 1) / 4
+// decode tables of ring degree n: the stage twiddles of e^{+2 pi i k / (n/2)}, and
+// the slot -> transform index map t_j = (5^j mod 2n - 1) / 4
 struct DecTables {
-  std::vector<double> twr, twi;  // per-stage twiddles of fft_pos_brev_in for length n/2
-  std::vector<uint32_t> brev;    // bit reversal over log2(n/2) bits
+  StageTwiddles stage;           // for length n/2
+  std::vector<uint32_t> brev;    // place of point k after bit reversal over log2(n/2) bits
   std::vector<uint32_t> slot_t;
 };
 const DecTables& dec_tables(int n) {
@@ -1046,29 +1128,19 @@ const DecTables& dec_tables(int n) {
   if (!slot) {
     auto t = std::make_unique<DecTables>();
     const int h = n / 2;
-    // stage of span len: e^{+2 pi i j / len}, j < len/2, at offset len/2 - 2;
-    // taken from the length-h table (index j h / len) so every stage uses the
-    // same rounded values as a single table would
-    std::vector<double> cr(h / 2), ci(h / 2);
+    std::vector<cplx> root(h / 2);
     for (int k = 0; k < h / 2; ++k) {
       const double ang = 2.0 * M_PI * (double)k / (double)h;
-      cr[k] = std::cos(ang);
-      ci[k] = std::sin(ang);
+      root[k] = cplx(std::cos(ang), std::sin(ang));
     }
-    t->twr.assign(h > 2 ? h - 2 : 0, 0.0);
-    t->twi.assign(h > 2 ? h - 2 : 0, 0.0);
-    for (int len = 4; len <= h; len <<= 1)
-      for (int j = 0; j < len / 2; ++j) {
-        t->twr[len / 2 - 2 + j] = cr[(size_t)j * (h / len)];
-        t->twi[len / 2 - 2 + j] = ci[(size_t)j * (h / len)];
-      }
+    t->stage.fill(h, root.data());
     int bits = 0;
     while ((1 << bits) < h) ++bits;
     t->brev.resize(h);
-    for (int k = 0; k < h; ++k) t->brev[k] = bitrev((uint32_t)k, bits);
+    for (int k = 0; k < h; ++k) t->brev[k] = (uint32_t)fft_at(bitrev((uint32_t)k, bits));
     const std::vector<u64>& e = fft_tables(n).e;
     t->slot_t.resize(h);
-    for (int j = 0; j < h; ++j) t->slot_t[j] = (uint32_t)((e[j] - 1) / 4);
+    for (int j = 0; j < h; ++j) t->slot_t[j] = (uint32_t)fft_at((e[j] - 1) / 4);
     slot = std::move(t);
   }
   return *slot;
@@ -1095,7 +1167,8 @@ int fa_decode(const fa_ctx* c, const uint64_t* res, int log_scale, double* out, 
   // transform of length N/2.
   const FftTables& tb = fft_tables(n);
   const DecTables& dt = dec_tables(n);
-  std::vector<double> re(h), im(h);
+  FftBuf buf(h);
+  double *re = buf.re, *im = buf.im;
   // One host thread: a client decodes its result blocks several at a time, and
   // threads started inside each decode made those concurrent calls several
   // times slower than serial ones.
@@ -1117,7 +1190,16 @@ int fa_decode(const fa_ctx* c, const uint64_t* res, int log_scale, double* out, 
     case 4: crt(std::integral_constant<int, 4>{}); break;
     default: crt(std::integral_constant<int, 0>{}); break;
   }
-  fft_pos_brev_in(re.data(), im.data(), h, dt.twr.data(), dt.twi.data());
+  // the transform (bit-reversed input): the span-2 stage, then the others
+  for (int i = 0; i < h; i += 2) {
+    const size_t s0 = fft_at(i);
+    const double ur = re[s0], ui = im[s0], vr = re[s0 + 1], vi = im[s0 + 1];
+    re[s0] = ur + vr;
+    im[s0] = ui + vi;
+    re[s0 + 1] = ur - vr;
+    im[s0 + 1] = ui - vi;
+  }
+  fft_stages(re, im, h, 4, dt.stage);
   const double inv_scale = std::ldexp(1.0, -log_scale);
   for (int j = 0; j < n_slots; ++j) out[j] = re[dt.slot_t[j]] * inv_scale;
   return FA_OK;
@@ -1146,30 +1228,16 @@ static int upload_int_pts(fa_ctx* c, const int64_t* coeffs, int n_pts, double* p
 // same rounded values).
 static int ensure_fft(fa_ctx* c) {
   std::lock_guard<std::mutex> lock(c->fft_mu);
-  if (c->d_fft_slot) return FA_OK;
+  if (c->d_fft) return FA_OK;
   const FftTables& tb = fft_tables(c->n);
-  const size_t n = c->n;
-  std::vector<uint32_t> slot(n);
-  for (size_t j = 0; j < n / 2; ++j) slot[(tb.e[j] - 1) / 2] = slot[(2 * n - tb.e[j] - 1) / 2] = (uint32_t)j;
-  double *root = nullptr, *twist = nullptr;
-  uint32_t* ds = nullptr;
-  int rc;
-  hipError_t e = hipSuccess;
-  if (!(rc = dev_alloc(&root, n)) && !(rc = dev_alloc(&twist, 2 * n)) && !(rc = dev_alloc(&ds, n))) {
-    e = hipMemcpy(root, tb.root_fwd.data(), n * 8, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(twist, tb.twist.data(), 2 * n * 8, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(ds, slot.data(), n * 4, hipMemcpyHostToDevice);
-    if (e != hipSuccess) rc = fail(FA_E_HIP, "encoding tables: %s", hipGetErrorString(e));
+  char* d = nullptr;
+  if (int rc = dev_alloc(&d, tb.device.size())) return rc;
+  const hipError_t e = hipMemcpy(d, tb.device.data(), tb.device.size(), hipMemcpyHostToDevice);
+  if (e != hipSuccess) {
+    (void)hipFree(d);
+    return fail(FA_E_HIP, "encoding tables: %s", hipGetErrorString(e));
   }
-  if (rc) {
-    (void)hipFree(root);
-    (void)hipFree(twist);
-    (void)hipFree(ds);
-    return rc;
-  }
-  c->d_fft_root = root;
-  c->d_fft_twist = twist;
-  c->d_fft_slot = ds;
+  c->d_fft = d;
   return FA_OK;
 }
 

@@ -89,13 +89,11 @@ struct fa_ctx {
   // runs there while the scores run on the caller's stream
   hipStream_t side = nullptr;
   hipEvent_t side_fork = nullptr, side_join = nullptr;
-  // tables of the float encoders (built by the first call that needs them):
-  // e^{-2 pi i k / N} for k < N/2 and e^{i pi k / N} for k < N as (re, im) pairs,
-  // and the slot whose value point t of the transform takes
+  // tables of the float encoders, uploaded by the first call that needs them:
+  // e^{-2 pi i k / N} for k < N/2, then e^{i pi k / N} for k < N, as (re, im)
+  // pairs, then the slot whose value point t of the transform takes
   std::mutex fft_mu;
-  double* d_fft_root = nullptr;
-  double* d_fft_twist = nullptr;
-  uint32_t* d_fft_slot = nullptr;
+  char* d_fft = nullptr;
   // device staging of fa_decrypt / fa_export_coeffs (client and test side),
   // grown on demand and reused; the mutex serialises callers on other threads
   std::mutex export_mu;
