@@ -1333,18 +1333,27 @@ int fa_encode_projection(fa_ctx* c, const float* W, int d_in, int r, int baby_st
 namespace {
 constexpr int kRotBatch = 16;  // most rotations key-switched per launch group
 
-// Rotations per launch group of one query's baby steps (1..kRotBatch;
-// FA_ROT_BATCH overrides it): 8 with several key-switch digits (measured
-// 0.05 ms faster than 16 on the 12-prime rerank level), 16 with one digit (the
-// fused special-prime kernel's launches stay large).  The environment is read
-// once, by a thread-safe static initialiser.
-int rot_batch(const fa_ctx* c) {
+// FA_ROT_BATCH (1..kRotBatch), or 0.  The environment is read once, by a
+// thread-safe static initialiser.
+int rot_batch_env() {
   static const int v = [] {
     const char* e = getenv("FA_ROT_BATCH");
     const int r = e ? atoi(e) : 0;
     return (r < 1 || r > kRotBatch) ? 0 : r;
   }();
-  return v ? v : (c->dnum > 1 ? 8 : kRotBatch);
+  return v;
+}
+// Rotations per lane that the baby steps' workspace is sized for
+int rot_batch(const fa_ctx* c) { return rot_batch_env() ? rot_batch_env() : c->dnum > 1 ? 8 : kRotBatch; }
+// Rotations per launch group of one query's baby steps: 16, or 8 where there are
+// more than two groups of 16 and each would write over 128 MiB of conversions.
+// 16 and 8 measured: N=2^15, 8+2 primes, B=32 and 64: 761 / 788 and 801 / 859 us;
+// N=2^14, 5+2, B=32: 337 / 369; N=2^16, 6+3, B=64: 1065 / 1126; N=2^16, 12+3, B=16:
+// 2113 / 2143, but B=64: 4888 / 4859.
+int rot_group(const fa_ctx* c, int B) {
+  if (rot_batch_env()) return rot_batch_env();
+  const size_t conv = (size_t)kRotBatch * 2 * c->L * c->n * 8;
+  return c->dnum == 1 || B - 1 <= 2 * kRotBatch || conv <= ((size_t)128 << 20) ? kRotBatch : 8;
 }
 
 struct Arena {
@@ -1449,35 +1458,34 @@ static void modup(fa_ctx* c, const double* cts, size_t ct_stride, int batch, dou
   fa::modup_fused(c, it.data(), batch, s, pass_b);
 }
 
-// ModDown of `count` polynomials u_i = u + i * np * N over Q u P (NTT form):
+// ModDown of `count` polynomials u_i (NTT form), their special primes' limbs at
+// sp + i * sp_st and, with pass_b, their ciphertext primes' at uq + i * np * N:
 // out_i = bases_i[pi_gal_i] + (u_i,Q - Conv_{P->Q}(u_i,P)) * P^-1.  The special-
-// prime limbs of u are overwritten (the row pass of their inverse transform;
+// prime limbs are overwritten (the row pass of their inverse transform;
 // inv_b_done: already done by the caller); conv is scratch.  With pass_b
 // false only the special-prime inverse and the conversion's first pass run
-// (bases, outs and gals unused): moddown_ks finishes.
-static void moddown_polys(fa_ctx* c, double* u, int count, double* conv, const double* const* bases,
-                          double* const* outs, const uint32_t* gals, hipStream_t s, bool pass_b = true,
-                          bool inv_b_done = false) {
+// (uq, bases, outs and gals unused): moddown_ks finishes.
+static void moddown_polys(fa_ctx* c, double* sp, size_t sp_st, int count, double* conv, const double* uq,
+                          const double* const* bases, double* const* outs, const uint32_t* gals, hipStream_t s,
+                          bool pass_b = true, bool inv_b_done = false) {
   const size_t n = c->n, L = c->L, np = c->np;
   if (!inv_b_done) {
     // the row pass of the inverse transform, in place; the fused ModDown
     // kernel finishes it
     fa::LimbBatch inv(c, s, false, true);
     for (int i = 0; i < count; ++i)
-      for (int k = 0; k < c->K; ++k) inv.add(u + (size_t)i * np * n + (L + k) * n, (int)L + k);
+      for (int k = 0; k < c->K; ++k) inv.add(sp + (size_t)i * sp_st + k * n, (int)L + k);
   }
   std::vector<fa::MdItem> it(count);
-  for (int i = 0; i < count; ++i) {
-    double* ui = u + (size_t)i * np * n;
-    it[i] = {ui + L * n, conv + (size_t)i * L * n, ui, pass_b ? bases[i] : nullptr, pass_b ? outs[i] : nullptr,
-             pass_b ? gals[i] : 1u};
-  }
+  for (int i = 0; i < count; ++i)
+    it[i] = {sp + (size_t)i * sp_st, conv + (size_t)i * L * n, pass_b ? uq + (size_t)i * np * n : nullptr,
+             pass_b ? bases[i] : nullptr, pass_b ? outs[i] : nullptr, pass_b ? gals[i] : 1u};
   fa::moddown_fused(c, it.data(), count, s, pass_b);
 }
 
 // Key switch and ModDown of `count` rotations: outs[j] = (c0s[j][pi] + ModDown(u_0),
 // ModDown(u_1)) with u = sum_i sigma(ext_i) key_i.  The special-prime part of u
-// goes through u (per rotation [2][np][N]); the ciphertext-prime part is formed
+// goes through u (per rotation [2][K][N]); the ciphertext-prime part is formed
 // inside the finishing kernel.  conv: per rotation [2][L][N] scratch.  b0s / b1s
 // (or null): added to the output polynomials.
 static void ks_moddown(fa_ctx* c, const fa::KsItem* ks, int count, const double* const* c0s, double* const* outs,
@@ -1496,10 +1504,10 @@ static void ks_moddown(fa_ctx* c, const fa::KsItem* ks, int count, const double*
     // kernel (measured faster at 2 and 3 primes; with more digits the fused
     // kernel's longer load phase made it slower)
     fa::ks_inv_b(c, ks, count, s, nq);
-    moddown_polys(c, u, 2 * count, conv, nullptr, nullptr, nullptr, s, false, true);
+    moddown_polys(c, u, (size_t)c->K * n, 2 * count, conv, nullptr, nullptr, nullptr, nullptr, s, false, true);
   } else {
-    fa::ks_inner(c, ks, count, false, s, c->L, nq);
-    moddown_polys(c, u, 2 * count, conv, nullptr, nullptr, nullptr, s, false);
+    fa::ks_inner(c, ks, count, s, nq);
+    moddown_polys(c, u, (size_t)c->K * n, 2 * count, conv, nullptr, nullptr, nullptr, nullptr, s, false);
   }
   std::vector<fa::MdKsItem> it(count);
   for (int j = 0; j < count; ++j)
@@ -1555,7 +1563,7 @@ static int rotations_from_ext(fa_ctx* c, const double* q, const double* ext, con
       auto it = c->keys.find(steps[r0 + j]);
       if (it == c->keys.end()) return fail(FA_E_NOKEY, "no rotation key for step %d", steps[r0 + j]);
       const uint32_t gal = galois(c->n, steps[r0 + j]);
-      ks[j] = {ext, q + L * n, it->second, ul + (size_t)j * 2 * np * n, nullptr, gal};
+      ks[j] = {ext, q + L * n, it->second, ul + (size_t)j * 2 * c->K * n, gal, 0u};
       c0s[j] = q;
     }
     ks_moddown(c, ks, rb, c0s, outs + r0, ul, cl, ls);
@@ -1584,7 +1592,7 @@ static int rotate_batch(fa_ctx* c, const double* cts, int nb, int step, double* 
   const uint32_t gal = galois(c->n, step);
   for (int b = 0; b < nb; ++b) {
     const double* ct = cts + (size_t)b * ctw;
-    ks[b] = {ext + (size_t)b * dn * np * n, ct + L * n, it->second, u + (size_t)b * 2 * np * n, nullptr, gal};
+    ks[b] = {ext + (size_t)b * dn * np * n, ct + L * n, it->second, u + (size_t)b * 2 * c->K * n, gal, 0u};
     c0s[b] = ct;
     c1s[b] = ct + L * n;
     douts[b] = outs + (size_t)b * ctw;
@@ -1636,7 +1644,7 @@ static int relin_batch(fa_ctx* c, const double* d, int count, double* out, Arena
     std::vector<double*> outs(nb);
     for (int j = 0; j < nb; ++j) {
       const double* dj = d + (size_t)(j0 + j) * d3;
-      ks[j] = {ext + (size_t)j * dn * np * n, dj + 2 * L * n, c->d_rlk, u + (size_t)j * 2 * np * n, nullptr, 1u};
+      ks[j] = {ext + (size_t)j * dn * np * n, dj + 2 * L * n, c->d_rlk, u + (size_t)j * 2 * c->K * n, 1u, 0u};
       c0s[j] = dj;
       b1s[j] = dj + L * n;
       outs[j] = out + (size_t)(j0 + j) * ctw;
@@ -1677,18 +1685,22 @@ static int baby_phase(fa_ctx* c, const double* q, int B, double* qrot, Arena& ar
   if (B < 2) return FA_OK;
   for (int b = 1; b < B; ++b)
     if (!c->keys.count(b)) return fail(FA_E_NOKEY, "no rotation key for baby step %d", b);
-  const int rb = std::max(1, std::min(rot_batch(c), B - 1));
   const int lanes = lanes_wanted();
   const size_t mark = ar.used;
+  if (ar.cap - ar.used < baby_ws(c, B)) return fail(FA_E_NOMEM, "workspace too small for the baby rotations");
   double* y = ar.take(L * n);
   double* ext = ar.take(dn * np * n);
-  double* u = ar.take((size_t)lanes * (rup((size_t)rb * 2 * np * n) / 8));
-  double* conv = ar.take((size_t)lanes * (rup((size_t)rb * 2 * L * n) / 8));
-  if (!y || !ext || !u || !conv) return fail(FA_E_NOMEM, "workspace too small for the baby rotations");
-  if (fa::small_ring(c)) {
-    ar.used = mark;
-    return baby_small(c, &q, 1, B, &qrot, ext, 0, u, (size_t)lanes * (rup((size_t)rb * 2 * np * n) / 8), s);
-  }
+  // the rest of the arena is free until the accumulators: a rotation needs its
+  // special primes' sums and its conversions of it
+  double* pool = (double*)(ar.base + ar.used);
+  const size_t pool_words = (ar.cap - ar.used) / 8;
+  ar.used = mark;
+  if (fa::small_ring(c)) return baby_small(c, &q, 1, B, &qrot, ext, 0, pool, pool_words, s);
+  const size_t u_item = 2 * (size_t)c->K * n, c_item = 2 * L * n;
+  const int fit = (int)std::min<size_t>(kRotBatch, pool_words / lanes / (u_item + c_item));
+  const int rb = std::max(1, std::min({rot_group(c, B), B - 1, fit}));
+  const size_t u_lane = rb * u_item, c_lane = rb * c_item;
+  double *u = pool, *conv = pool + lanes * u_lane;
   int rc = ensure_lanes(c, lanes);
   if (rc) return rc;
   modup(c, q, ctw, 1, y, L * n, ext, dn * np * n, s);
@@ -1701,12 +1713,9 @@ static int baby_phase(fa_ctx* c, const double* q, int B, double* qrot, Arena& ar
   const int nbatch = (B - 1 + rb - 1) / rb;
   const int bl = std::min(lanes, nbatch);
   if ((rc = fork_lanes(c, s, bl))) return rc;
-  rc = rotations_from_ext(c, q, ext, steps.data(), B - 1, outs.data(), u, conv, s, bl, rb,
-                          rup((size_t)rb * 2 * np * n) / 8, rup((size_t)rb * 2 * L * n) / 8);
+  rc = rotations_from_ext(c, q, ext, steps.data(), B - 1, outs.data(), u, conv, s, bl, rb, u_lane, c_lane);
   if (rc) return rc;
-  if ((rc = join_lanes(c, s, bl))) return rc;
-  ar.used = mark;
-  return FA_OK;
+  return join_lanes(c, s, bl);
 }
 
 // Baby rotations of n_q queries, qrots[j][b-1] = Rotate(qs[j], b), b = 1..B-1:
@@ -1755,7 +1764,7 @@ static int baby_phase_batch(fa_ctx* c, const double* const* qs, int nq, int B, d
       const double* key = c->keys[b];
       const uint32_t gal = galois(c->n, b);
       for (int j = 0; j < nq; ++j, ++m) {
-        ks[m] = {ext + (size_t)j * (rup(ext_w) / 8), qs[j] + L * n, key, ul + (size_t)m * 2 * np * n, nullptr, gal};
+        ks[m] = {ext + (size_t)j * (rup(ext_w) / 8), qs[j] + L * n, key, ul + (size_t)m * 2 * c->K * n, gal, 0u};
         c0s[m] = qs[j];
         outs[m] = qrots[j] + (size_t)(b - 1) * ctw;
       }
@@ -1850,7 +1859,7 @@ static int giant_phase(fa_ctx* c, const double* acc, int nb, int G, int B, doubl
       douts[2 * blk] = outs[b0 + blk];
       douts[2 * blk + 1] = outs[b0 + blk] + L * n;
     }
-    moddown_polys(c, usum, 2 * cb, gconv, bases.data(), douts.data(), gals.data(), s);
+    moddown_polys(c, usum + L * n, np * n, 2 * cb, gconv, usum, bases.data(), douts.data(), gals.data(), s);
   }
   ar.used = mark;
   return FA_OK;

@@ -176,23 +176,19 @@ struct MdKsItem {
 // XCD so the key words are read from HBM once per group.  count % nq == 0.
 void moddown_ks(const fa_ctx* c, const MdKsItem* items, int count, hipStream_t s, int nq = 1);
 
-// Key-switch inner product with the automorphism folded in:
-// u[j] (+)= sum_i sigma_{g_j}(ext[j or 0]_i) * key_j[i]  over all np primes.
+// Key-switch inner product on the special primes with the automorphism folded in:
+// u_h = sum_i sigma_g(ext_i) * key_i[h], h = 0, 1.
 struct KsItem {
   const double* ext;  // [dnum][np][N]
   const double* c1;   // [L][N] NTT form: the digits' own limbs
   const double* key;  // [dnum][2][np][N]
-  double* u;          // [2][np][N]
-  const double* c0;   // [L][N] or null: adds P * sigma(c0) to u0 on the ciphertext primes
+  double* u;          // [2][K][N]
   uint32_t gal;       // Galois element
   uint32_t inv_gal;   // gal^-1 mod 2N (set by the launcher)
 };
-// t0 > 0: only primes t0..np-1 (the special primes when t0 = L)
 // nq > 1: items grouped by key as for moddown_ks (count % nq == 0)
-void ks_inner(const fa_ctx* c, const KsItem* items, int count, bool accumulate, hipStream_t s, int t0 = 0,
-              int nq = 1);
-// The special-prime part of ks_inner (no c0 term, not accumulated) fused with
-// the first pass of its inverse transform: it.u's special limbs leave holding
+void ks_inner(const fa_ctx* c, const KsItem* items, int count, hipStream_t s, int nq = 1);
+// ks_inner fused with the first pass of its inverse transform: it.u leaves holding
 // what k_ntt_inv_b would produce from ks_inner's output (ntt_inv_a finishes).
 // One-digit contexts (dnum == 1) only; does nothing otherwise.
 void ks_inv_b(const fa_ctx* c, const KsItem* items, int count, hipStream_t s, int nq = 1);

@@ -823,8 +823,8 @@ __global__ __launch_bounds__(256) void k_ntt_inv_b(LimbList ll, const DevPrime* 
 }
 
 // ---------------------------------------------------------------------------
-// key-switch inner product with the automorphism folded into the read of the
-// extended digits; a digit's own limbs are read from c1 itself
+// key-switch inner product on the special primes with the automorphism folded
+// into the read of the extended digits
 // ---------------------------------------------------------------------------
 #define FA_MAXKS 32
 struct KsArgs {
@@ -833,27 +833,25 @@ struct KsArgs {
 
 template <int DNUM>
 __global__ __launch_bounds__(256) void k_ks_inner(KsArgs args, const DevPrime* __restrict__ pr, int logn, int L,
-                                                  int np, int alpha, int accumulate, int t0, int nq, int ngroup) {
-  const int n = 1 << logn;
+                                                  int np, int nq, int ngroup) {
+  const int n = 1 << logn, K = np - L;
   int kx, tr, item;
   if (nq == 1) {
     int src;
-    if (!ks_decode_src(blockIdx.x, n / 256, np - t0, ngroup, src, tr, item)) return;
+    if (!ks_decode_src(blockIdx.x, n / 256, K, ngroup, src, tr, item)) return;
     kx = (int)(perm((uint32_t)src * 256u, args.it[item].inv_gal, logn) / 256u);  // see k_moddown_ks_b
-  } else if (!ks_decode(blockIdx.x, n / 256, np - t0, nq, ngroup, kx, tr, item)) {
+  } else if (!ks_decode(blockIdx.x, n / 256, K, nq, ngroup, kx, tr, item)) {
     return;
   }
   const int k = kx * 256 + threadIdx.x;
-  const int t = t0 + tr;
+  const int t = L + tr;
   const fa::KsItem& it = args.it[item];
   const double q = pr[t].q, qinv = pr[t].qinv;
   const uint32_t kk = perm((uint32_t)k, it.gal, logn);
-  const int own = t < L ? t / alpha : -1;
   double x[DNUM], kb[DNUM], ka[DNUM];
 #pragma unroll
   for (int i = 0; i < DNUM; ++i) {
-    const double* src = i == own ? it.c1 + (size_t)t * n : it.ext + ((size_t)i * np + t) * n;
-    x[i] = src[kk];
+    x[i] = it.ext[((size_t)i * np + t) * n + kk];
     kb[i] = __builtin_nontemporal_load(it.key + (((size_t)i * 2 + 0) * np + t) * n + k);
     ka[i] = __builtin_nontemporal_load(it.key + (((size_t)i * 2 + 1) * np + t) * n + k);
   }
@@ -863,17 +861,8 @@ __global__ __launch_bounds__(256) void k_ks_inner(KsArgs args, const DevPrime* _
     acc0 += mul(x[i], kb[i], q, qinv);
     acc1 += mul(x[i], ka[i], q, qinv);
   }
-  // P * sigma(c0) on the ciphertext primes: ModDown of the sum then returns
-  // ModDown(sum u0) + sigma(c0) exactly, so the giant-step c0 terms ride along.
-  if (it.c0 && t < L) acc0 += mul(it.c0[(size_t)t * n + kk], pr[t].pmod, q, qinv);
-  double* u0 = it.u + (size_t)t * n + k;
-  double* u1 = it.u + ((size_t)np + t) * n + k;
-  if (accumulate) {
-    acc0 += *u0;
-    acc1 += *u1;
-  }
-  *u0 = canon_full(acc0, q, qinv);
-  *u1 = canon_full(acc1, q, qinv);
+  it.u[(size_t)tr * n + k] = canon_full(acc0, q, qinv);
+  it.u[((size_t)K + tr) * n + k] = canon_full(acc1, q, qinv);
 }
 
 // Key-switch sum on the special primes fused with the first pass of its
@@ -919,7 +908,7 @@ __global__ __launch_bounds__(256) void k_ks_inv_b(KsArgs args, const DevPrime* _
       y1[j] += mul(x, a, q, qinv);
     }
   }
-  double* out = it.u + (size_t)t * n;
+  double* out = it.u + (size_t)tr * n;
 #pragma unroll
   for (int j = 0; j < 16; ++j) sm[lds_row(j, threadIdx.x)] = reduce(y0[j], q, qinv);
   __syncthreads();
@@ -928,7 +917,7 @@ __global__ __launch_bounds__(256) void k_ks_inv_b(KsArgs args, const DevPrime* _
 #pragma unroll
   for (int j = 0; j < 16; ++j) sm[lds_row(j, threadIdx.x)] = reduce(y1[j], q, qinv);
   __syncthreads();
-  inv_b_rows(sm, out + (size_t)np * n, tile * 16, T, F, q, qinv);
+  inv_b_rows(sm, out + (size_t)(np - L) * n, tile * 16, T, F, q, qinv);
 }
 
 // ---------------------------------------------------------------------------
@@ -1949,14 +1938,13 @@ void moddown_ks(const fa_ctx* c, const MdKsItem* items, int count, hipStream_t s
 }
 
 template <int DNUM>
-static void launch_ks(const fa_ctx* c, const KsArgs& a, int m, bool accumulate, hipStream_t s, int t0, int nq) {
+static void launch_ks(const fa_ctx* c, const KsArgs& a, int m, hipStream_t s, int nq) {
   const int ngroup = m / nq;
-  dim3 g(ks_grid(c->n / 256, c->np - t0, nq, ngroup));
-  hipLaunchKernelGGL(k_ks_inner<DNUM>, g, dim3(256), 0, s, a, c->d_pr, c->logn, c->L, c->np, c->alpha,
-                     accumulate ? 1 : 0, t0, nq, ngroup);
+  dim3 g(ks_grid(c->n / 256, c->K, nq, ngroup));
+  hipLaunchKernelGGL(k_ks_inner<DNUM>, g, dim3(256), 0, s, a, c->d_pr, c->logn, c->L, c->np, nq, ngroup);
 }
 
-void ks_inner(const fa_ctx* c, const KsItem* items, int count, bool accumulate, hipStream_t s, int t0, int nq) {
+void ks_inner(const fa_ctx* c, const KsItem* items, int count, hipStream_t s, int nq) {
   const int chunk = (FA_MAXKS / nq) * nq;
   for (int off = 0; off < count; off += chunk) {
     KsArgs a;
@@ -1966,14 +1954,14 @@ void ks_inner(const fa_ctx* c, const KsItem* items, int count, bool accumulate, 
       a.it[i].inv_gal = inv_galois(a.it[i].gal, c->logn);
     }
     switch (c->dnum) {
-      case 1: launch_ks<1>(c, a, m, accumulate, s, t0, nq); break;
-      case 2: launch_ks<2>(c, a, m, accumulate, s, t0, nq); break;
-      case 3: launch_ks<3>(c, a, m, accumulate, s, t0, nq); break;
-      case 4: launch_ks<4>(c, a, m, accumulate, s, t0, nq); break;
-      case 5: launch_ks<5>(c, a, m, accumulate, s, t0, nq); break;
-      case 6: launch_ks<6>(c, a, m, accumulate, s, t0, nq); break;
-      case 7: launch_ks<7>(c, a, m, accumulate, s, t0, nq); break;
-      case 8: launch_ks<8>(c, a, m, accumulate, s, t0, nq); break;
+      case 1: launch_ks<1>(c, a, m, s, nq); break;
+      case 2: launch_ks<2>(c, a, m, s, nq); break;
+      case 3: launch_ks<3>(c, a, m, s, nq); break;
+      case 4: launch_ks<4>(c, a, m, s, nq); break;
+      case 5: launch_ks<5>(c, a, m, s, nq); break;
+      case 6: launch_ks<6>(c, a, m, s, nq); break;
+      case 7: launch_ks<7>(c, a, m, s, nq); break;
+      case 8: launch_ks<8>(c, a, m, s, nq); break;
       default: break;
     }
   }
