@@ -13,11 +13,13 @@
 //   mulc(a, w, w/q):  for |a| <= c*q the quotient estimate is off by at most
 //     0.375c, so |result| <= (0.5 + 0.375c) q; exact for |a| <= 8q.
 //   mul(a, b):        |a|, |b| <= q  ->  |result| <= 0.75 q.
-//   reduce(x):        |x| < 2^52    ->  |result| <= q/2 (+ rounding slack).
-// Forward NTT values stay within 5.82 q (stages alternate lazy and reduced
-// butterflies, see ct_bfly), inverse NTT values within 2 q; every transform
-// output that leaves a kernel is either canonicalised or feeds a mulc / mul
-// whose operand stays within 8 q.
+//   mul(a, w) with |a| <= c*q and |w| <= q bounds the same way as mulc: its
+//     quotient estimate carries the same three roundings.
+//   reduce(x):        |x| < 2^53    ->  |result| <= q/2 (+ rounding slack).
+// Forward NTT values stay within 7.8 q (see ct_bfly and col_reduces), inverse
+// NTT values within 4 q (see gs_bfly); every transform output that leaves a
+// kernel is either canonicalised or feeds a mulc / mul whose operand stays
+// within 8 q.
 
 #include <hip/hip_runtime.h>
 
@@ -31,12 +33,12 @@
 namespace {
 
 // Cooley-Tukey butterfly (forward): (x, y) -> (x + w y, x - w y).  With R
-// false x is not reduced first: the passes below reduce on odd stages only.
-// With c the bound (in units of q) of the stage's inputs, a reduced stage
-// leaves 1 + 0.375c and a lazy one 1.375c + 0.5; alternating from c <= 1 the
-// bound settles at 2.45 after reduced and 3.87 after lazy stages, and two lazy
-// stages in a row (an odd first pass meeting the next pass's stage 0) reach
-// 5.82: always inside the 8q of mulc's exactness and below 2^53.
+// false x is not reduced first.  With c the bound (in units of q) of the stage's
+// inputs, a reduced stage leaves 1 + 0.375c and a lazy one 1.375c + 0.5.  The row
+// passes alternate lazy and reduced stages, lazy first: from the 5.3 that the
+// fused column passes may leave (col_reduces) they reach 7.8 once and fall to
+// 3.9, 5.9, 3.2, ...; the plain column passes alternate too and leave at most
+// 3.9.  Always inside the 8q of the product's exactness and below 2^53.
 template <bool R = true>
 __device__ __forceinline__ void ct_bfly(double& x, double& y, double w, double q, double qinv) {
   const double u = R ? reduce(x, q, qinv) : x;
@@ -190,9 +192,12 @@ struct MuArgs {
 // representatives around 0 instead of canonical ones.
 //
 // 512 threads hold eight words each, so the columns take two or three passes of
-// two or three stages with an LDS exchange between them.  (With sixteen words on
+// two or three stages with an LDS exchange between them.  With sixteen words on
 // 256 threads, one exchange, the kept coefficients took 232-256 registers and
-// two waves per SIMD; eight words leave room for four.)
+// two waves per SIMD; eight words leave room for four.  At N = 2^16 with 12+3
+// primes a ModDown launch of 16 polynomials went from 91 to 74 us beside the
+// other lane's work (its 126 MB are 30 us at a copy's 4.8 TB/s); the rest of the
+// gain is in small launches, see conv_groups.
 template <int SA>
 struct ColPass {
   static constexpr int H = 1 << SA, COLS = 4096 >> SA, T = 512;

@@ -11,9 +11,14 @@
 //   k_sr_ksinv    key-switch sum on a special prime and its inverse transform,
 //   k_sr_finish   conversion to one ciphertext prime, forward transform, the
 //                 key-switch sum on that prime, ModDown and the additions.
-// With one special prime (one limb per digit) the first and the third run
-// inside the second and the fourth when there are workgroups to spare
-// (FUSED): a rotation is two launches.
+// With one special prime (one limb per digit) the first runs inside the second
+// and the third's inverse inside the fourth when there are workgroups to spare
+// (FUSED), its sums formed before by k_sr_special: a rotation is three launches,
+// otherwise four.  Measured: a rotation at N = 2^13, 3+1 primes 43.5 -> 31.0 us,
+// the 7-step row fold 340 -> 227 us, twenty-four calls of all kinds at N = 2^11 to
+// 2^13 1.9 times as fast on average.  What is left of a rotation: the inverse
+// transform on one CU (4.8 us, twice: 7.7k clocks of issue and 4k of LDS), the
+// quarter's share of the forward one, and 2-3 us a launch.
 //
 // Bounds (in units of q, see fa_kernels.hip for the products): fwd_reduces()
 // and inv_reduces() place the reductions stage by stage so that a product's
