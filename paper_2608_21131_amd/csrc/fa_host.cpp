@@ -867,8 +867,8 @@ int fa_has_relin_key(const fa_ctx* c) { return c && c->d_rlk ? 1 : 0; }
 
 
 // The context's device staging of the client calls: at least 2 * words words at
-// c->d_export, grown on demand.  The caller holds export_mu until its work on the
-// staging is synchronised.
+// c->d_export, grown on demand.  The caller holds export_mu until release_export
+// has synchronised its work on the staging.
 static int ensure_export(fa_ctx* c, size_t words) {
   if (c->export_words >= words) return FA_OK;
   (void)hipFree(c->d_export);
@@ -877,6 +877,16 @@ static int ensure_export(fa_ctx* c, size_t words) {
   if (int rc = dev_alloc(&c->d_export, 2 * words)) return rc;
   c->export_words = words;
   return FA_OK;
+}
+
+// End of a call's use of the staging: synchronised on every path, a failed copy or
+// launch (he, rc) included, because the next caller, perhaps on another stream,
+// takes the same memory.  Returns the call's first error.
+static int release_export(const char* fn, int rc, hipError_t he, hipStream_t s) {
+  const hipError_t se = hipStreamSynchronize(s);
+  if (rc) return rc;
+  if (he == hipSuccess) he = se;
+  return he == hipSuccess ? FA_OK : fail(FA_E_HIP, "%s: %s", fn, hipGetErrorString(he));
 }
 
 int fa_encrypt(fa_ctx* c, const int64_t* m, int32_t log_scale, const uint64_t* a, const int64_t* e, fa_buf* ct,
@@ -899,17 +909,17 @@ int fa_encrypt(fa_ctx* c, const int64_t* m, int32_t log_scale, const uint64_t* a
   int64_t* dm = reinterpret_cast<int64_t*>(du + L * n);
   double* dv = c->d_export + (L + 1) * n;
   double* dct = (double*)ct->dev;
-  HIPCHK(hipMemcpyAsync(du, a, L * n * 8, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(dm, me.data(), n * 8, hipMemcpyHostToDevice, s));
-  fa::u64_to_res(du, L * n, dct + L * n, s);
-  fa::ntt_fwd_strided(c, dct + L * n, n, (int)L, (int)L, 0, s);
-  fa::int_to_res(c, dm, 1, (int)L, dv, s);
-  fa::ntt_fwd_strided(c, dv, n, (int)L, (int)L, 0, s);
-  fa::enc_combine(c, dct, dv, s);
-  // synchronised on a failed launch too: the staging is the next caller's
-  rc = check_launch("fa_encrypt");
-  HIPCHK(hipStreamSynchronize(s));
-  if (rc) return rc;
+  hipError_t he = hipMemcpyAsync(du, a, L * n * 8, hipMemcpyHostToDevice, s);
+  if (he == hipSuccess) he = hipMemcpyAsync(dm, me.data(), n * 8, hipMemcpyHostToDevice, s);
+  if (he == hipSuccess) {
+    fa::u64_to_res(du, L * n, dct + L * n, s);
+    fa::ntt_fwd_strided(c, dct + L * n, n, (int)L, (int)L, 0, s);
+    fa::int_to_res(c, dm, 1, (int)L, dv, s);
+    fa::ntt_fwd_strided(c, dv, n, (int)L, (int)L, 0, s);
+    fa::enc_combine(c, dct, dv, s);
+    rc = check_launch("fa_encrypt");
+  }
+  if ((rc = release_export("fa_encrypt", rc, he, s))) return rc;
   out_set(c, ct, 2, 1, log_scale);
   return FA_OK;
 }
@@ -973,18 +983,17 @@ static int export_polys(fa_ctx* c, const double* src, int n_polys, uint64_t* out
   if (int rc = ensure_export(c, words)) return rc;
   double* tmp = c->d_export;
   uint64_t* du = reinterpret_cast<uint64_t*>(c->d_export + c->export_words);
-  if (decrypt) {
-    fa::dec_combine(c, src, tmp, s);
-  } else {
-    HIPCHK(hipMemcpyAsync(tmp, src, words * 8, hipMemcpyDeviceToDevice, s));
+  hipError_t he = hipSuccess;
+  if (decrypt) fa::dec_combine(c, src, tmp, s);
+  else he = hipMemcpyAsync(tmp, src, words * 8, hipMemcpyDeviceToDevice, s);
+  int rc = FA_OK;
+  if (he == hipSuccess) {
+    fa::ntt_inv_strided(c, tmp, n, (int)(n_polys * L), (int)L, 0, s);
+    fa::res_to_u64(tmp, words, du, s);
+    rc = check_launch("export");
+    if (!rc) he = hipMemcpyAsync(out, du, words * 8, hipMemcpyDeviceToHost, s);
   }
-  fa::ntt_inv_strided(c, tmp, n, (int)(n_polys * L), (int)L, 0, s);
-  fa::res_to_u64(tmp, words, du, s);
-  int rc = check_launch("export");
-  if (rc) return rc;
-  HIPCHK(hipMemcpyAsync(out, du, words * 8, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
-  return FA_OK;
+  return release_export("export", rc, he, s);
 }
 
 int fa_decrypt(fa_ctx* c, const fa_buf* ct, uint64_t* out, void* stream) {

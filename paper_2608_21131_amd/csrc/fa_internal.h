@@ -94,10 +94,11 @@ struct fa_ctx {
   // pairs, then the slot whose value point t of the transform takes
   std::mutex fft_mu;
   char* d_fft = nullptr;
-  // device staging of fa_decrypt / fa_export_coeffs (client and test side),
-  // grown on demand and reused; the mutex serialises callers on other threads
+  // device staging of fa_encrypt / fa_decrypt / fa_export_coeffs (client and test
+  // side), grown on demand and reused; the mutex serialises callers on other
+  // threads and is held until the call's work on the staging is synchronised
   std::mutex export_mu;
-  double* d_export = nullptr;     // [2][words]: coefficient transform, then u64 residues
+  double* d_export = nullptr;     // [2][words]: coefficient transform, then u64 residues (see fa_encrypt for its own)
   size_t export_words = 0;
 };
 
