@@ -34,6 +34,35 @@ __device__ __forceinline__ double canon_full(double x, double q, double qinv) {
   return x < 0.0 ? x + q : x;
 }
 
+// A key-switch sum over words that come straight from a row pass (within 2.66 q, see
+// ct_bfly in fa_kernels.hip; a product with a canonical word is then within
+// 0.5 + 0.375 * 2.66): from a reduced word it takes kSumDigits of them and one
+// product of two canonical words before it could leave 8 q and 2^53, above which
+// integers are no longer exact.
+constexpr int kSumDigits = 4, kMaxDigits = 8;
+constexpr double kRowWord = 2.66;
+static_assert(0.5 + kSumDigits * (0.5 + 0.375 * kRowWord) + 0.75 < 8.0, "a sum stays exact");
+static_assert(2 * kSumDigits >= kMaxDigits, "one reduction among the digits is enough");
+// Digit i of DNUM of both polynomials' sums: s_h[j] += x[j] key_h[stride j].
+template <int DNUM, int R>
+__device__ __forceinline__ void add_digit(double (&s0)[R], double (&s1)[R], const double (&x)[R],
+                                          const double* __restrict__ key0, const double* __restrict__ key1, int stride,
+                                          int i, double q, double qinv) {
+  static_assert(DNUM <= kMaxDigits, "see kSumDigits");
+  if (DNUM > kSumDigits && i == kSumDigits) {
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      s0[j] = reduce(s0[j], q, qinv);
+      s1[j] = reduce(s1[j], q, qinv);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    s0[j] += mul(x[j], key0[stride * j], q, qinv);
+    s1[j] += mul(x[j], key1[stride * j], q, qinv);
+  }
+}
+
 // Index permutation of the Galois automorphism X -> X^gal in NTT order:
 // output slot i of the forward transform holds a(psi^(2 brev(i) + 1)), so
 // sigma(a)^[i] = a^[pi(i)] with 2 brev(pi(i)) + 1 = gal (2 brev(i) + 1) mod 2N.

@@ -20,6 +20,8 @@
 // NTT values within 4 q (see gs_bfly); every transform output that leaves a
 // kernel is either canonicalised or feeds a mulc / mul whose operand stays
 // within 8 q.
+// Sums of up to eight products of canonical words stay within 6 q; the giant
+// steps' sums, over words of a row pass, are reduced after four (add_digit).
 
 #include <hip/hip_runtime.h>
 
@@ -1036,11 +1038,7 @@ __global__ __launch_bounds__(256) void k_giant_ks(GiantArgs a, const DevPrime* _
         }
         __syncthreads();  // the next digit's pass reuses the LDS tile
       }
-#pragma unroll
-      for (int j = 0; j < ROWS; ++j) {
-        acc0[j] += mul(x[j], kb[256 * j], q, qinv);
-        acc1[j] += mul(x[j], ka[256 * j], q, qinv);
-      }
+      add_digit<DNUM>(acc0, acc1, x, kb, ka, 256, i, q, qinv);
     }
     if (t < L) {
       const double* __restrict__ c0 = accg + (size_t)t * n;
