@@ -13,7 +13,7 @@ from paper_2608_21131_amd import gen
 pytestmark = pytest.mark.gpu
 
 SETS = [(14, 3, 1), (14, 5, 2), (14, 2, 3), (15, 4, 3), (15, 3, 4), (15, 2, 1), (16, 2, 1), (16, 3, 2), (16, 5, 4)]
-common.PARAMS.update({f"c{logn}_{L}_{K}": (logn, L, K) for logn, L, K in SETS})
+common.PARAMS.update({f"c{logn}_{L}_{K}": (logn, L, K) for logn, L, K in SETS + [(14, 6, 1)]})
 
 
 # one ciphertext: the targets split into groups; three or five: fewer groups, then one
@@ -50,11 +50,30 @@ def test_rescale(logn, L, n_polys):
     assert np.array_equal(got, ckks.Oracle(par).rescale(x))
 
 
-# giant sums split into groups: 7 giants in up to 7 groups, 5 in uneven ones, one alone, and 63 (two
-# launches, the second adding to the first: not split); from 6 blocks on fewer groups
-@pytest.mark.parametrize("logn,L,K,d,B,blocks", [(14, 3, 1, 16, 2, 1), (14, 5, 2, 64, 1, 1), (15, 3, 4, 32, 4, 2),
-                                                 (16, 2, 1, 8, 4, 1), (14, 5, 2, 16, 2, 6), (14, 2, 3, 8, 1, 9)])
-def test_split_giant_sums(logn, L, K, d, B, blocks):
+def giant_groups(logn, L, K, ng, nb):
+    """Groups the giants of one launch are split into on two lanes, as the library's rule has them: the
+    chip's 512 workgroup places, the sums' scratch (one part per group after the first, in the
+    row-passed c1 of the ModUps), the giants and eight bound them; more than 32 giants are not split."""
+    np_, n = L + K, 1 << logn
+    if ng > 32:
+        return 1
+    parts = 2 * max(nb, ng) * L * n // (nb * 2 * np_ * n)
+    g = max(1, min(512 // ((n >> 12) * np_ * nb), 1 + parts, ng, 8))
+    per = -(-ng // g)
+    return -(-ng // per)
+
+
+# giant sums by the groups they are split into: one giant a group (3 and 7 giants, six digits in the
+# latter), the cap of eight groups with a short last one (15 and 31), 7 giants in four and in three groups,
+# two blocks, splits at N = 2^16, and one group: a single giant, 63 giants (two launches, the second adding
+# to the first), so many blocks that the scratch holds no part (6, 9)
+@pytest.mark.parametrize("logn,L,K,d,B,blocks,groups", [
+    (14, 3, 1, 16, 4, 1, 3), (14, 6, 1, 16, 2, 1, 7), (14, 3, 1, 16, 1, 1, 8), (14, 3, 1, 32, 1, 1, 8),
+    (14, 3, 1, 16, 2, 1, 4), (14, 3, 1, 16, 2, 2, 3), (15, 3, 4, 32, 4, 2, 2), (16, 2, 1, 16, 2, 1, 4),
+    (16, 2, 1, 32, 2, 1, 8), (16, 2, 1, 8, 4, 1, 1), (14, 5, 2, 64, 1, 1, 1), (14, 5, 2, 16, 2, 6, 1),
+    (14, 2, 3, 8, 1, 9, 1)])
+def test_split_giant_sums(logn, L, K, d, B, blocks, groups):
+    assert giant_groups(logn, L, K, d // B - 1, blocks) == groups
     p = Pair(f"c{logn}_{L}_{K}", wid=72)
     g = np.random.default_rng(d + blocks)
     keys = p.keys(ckks.steps_for_bsgs(d, B))
