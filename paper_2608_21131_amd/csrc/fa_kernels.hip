@@ -196,10 +196,11 @@ struct MuArgs {
 // 512 threads hold eight words each, so the columns take two or three passes of
 // two or three stages with an LDS exchange between them.  With sixteen words on
 // 256 threads, one exchange, the kept coefficients took 232-256 registers and
-// two waves per SIMD; eight words leave room for four.  At N = 2^16 with 12+3
-// primes a ModDown launch of 16 polynomials went from 91 to 74 us beside the
-// other lane's work (its 126 MB are 30 us at a copy's 4.8 TB/s); the rest of the
-// gain is in small launches, see conv_groups.
+// two waves per SIMD; eight words leave room for four (128 registers, of which
+// ModDown at N = 2^15 spills 2 with 3 special primes and 6 with 4).  At N = 2^16
+// with 12+3 primes a ModDown launch of 16 polynomials went from 91 to 74 us beside
+// the other lane's work (its 126 MB are 30 us at a copy's 4.8 TB/s); the rest of
+// the gain is in small launches, see conv_groups.
 template <int SA>
 struct ColPass {
   static constexpr int H = 1 << SA, COLS = 4096 >> SA, T = 512;
@@ -629,8 +630,11 @@ template <class St>
 __device__ __forceinline__ void fwd_b_body(double* a, const St& st, const double* __restrict__ T,
                                            const double* __restrict__ F, double q, double qinv, int logn,
                                            double* sm) {
-  // 16 on every ring that comes here; kept out of the compiler's sight, which
-  // schedules k_giant_ks half as fast when it knows fwd_b_lds's trip counts
+  // 16 on every ring that comes here (N >= 2^14), but not as a constant: with one,
+  // all callers of fwd_b_lds pass at most 16 rows, the compiler drops its loops
+  // before it inlines it, and k_giant_ks comes out at 160 registers instead of 206
+  // and slower.  Three blocks at N = 2^14, 8+1 primes, d = 64, B = 8: 670 against
+  // 429 us; a rerank level 5423 against 4841 us.
   const int rows = (1 << logn >> 8) < 16 ? (1 << logn >> 8) : 16;
   const int row0 = blockIdx.x * rows;
   fwd_b_lds(a, row0, rows, T, F, q, qinv, sm);
@@ -640,7 +644,7 @@ __device__ __forceinline__ void fwd_b_body(double* a, const St& st, const double
   // same in k_moddown_ks_b: a product with its rescale at N = 2^16, 12 primes
   // 147.3 -> 139.4 us, a rerank level at 3 primes 1217 -> 1191 us, a membership
   // scan 6.08 -> 5.97 ms
-  constexpr int FIN = 4;  // divides the rows of every ring (four at N = 2^10)
+  constexpr int FIN = 4;  // divides the rows
   const size_t i0 = (size_t)row0 * 256 + threadIdx.x;
   for (int r = 0; r < rows; r += FIN) {
     typename St::Op o[FIN];
@@ -970,7 +974,9 @@ __global__ __launch_bounds__(256) void k_ks_inv_b(KsArgs args, const DevPrime* _
 // runs.  Where the (tile, prime, block) triples leave the chip's 512 places (two
 // workgroups a CU) more than half empty, the giants are split into groups with
 // sums of their own, added by k_sum_parts: one block at N = 2^16 and 12+3 primes
-// (240 triples, 7 giants) took 210 us in one group.
+// (240 triples, 7 giants) took 210 us in one group.  The parts lie in the ModUps'
+// scratch, which bounds them too: it holds giants / blocks * L / (L + K) parts with
+// the default two lanes (half of that with one), none from blocks >= giants on.
 // ---------------------------------------------------------------------------
 #define FA_MAXG 32
 struct GiantArgs {

@@ -89,6 +89,8 @@ __device__ __forceinline__ int word(int v, int m) {
 // Group v of the pass holds stage s1's 2^s1 words at v (E - 1) + 2^s1 - 1.
 // PRE false (launches that fill the chip): read where they are used; the
 // registers saved let two workgroups share a CU, which hides as much.
+// The largest of either kind spill: k_sr_ksinv at N = 2^13 4 registers of 256 (PRE),
+// k_sr_modup at N = 2^10 with two primes a digit 8 of 128.
 template <int LOGN, bool PRE>
 struct Twiddles {
   double w[PRE ? pass_count(LOGN) - 1 : 1][PRE ? 15 : 1];
