@@ -4,6 +4,7 @@
     python -m paper_2608_21131_amd.rocprof_summary trace KERNEL_TRACE.csv
     python -m paper_2608_21131_amd.rocprof_summary valu VALUBUSY.csv
     python -m paper_2608_21131_amd.rocprof_summary waves SQ1.csv [SQ2.csv ...]
+    (each with --mark NAME)
 
 `traffic` takes the counter_collection.csv of two `rocprofv3 --pmc FETCH_SIZE` /
 `--pmc WRITE_SIZE` runs of `bench.py --copy-calib ...`.  The run's calibration
@@ -17,6 +18,10 @@ timed step.  `trace` lists the kernels of the same span with their durations,
 `waves` sums SQ counters (one or more `--pmc SQ_...` runs, SQ_WAVE_CYCLES
 among them) over the same span and gives each as a fraction of the kernel's
 wave-cycles.
+
+With `--mark NAME` as the last arguments the span is what lies between the last
+two dispatches whose kernel name holds NAME: one pass of a program that launches
+such a kernel (any that the library does not use) after each pass.
 """
 import csv
 import hashlib
@@ -27,6 +32,7 @@ from collections import OrderedDict
 
 GIB = 1 << 30
 MAC = "k_mac_diag"
+MARK = None  # kernel that ends a pass (--mark)
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -56,13 +62,14 @@ def _name(k):
 
 
 def _span(rows):
-    """Rows of the dispatches after the second-to-last multiply-accumulate launch up to the last one
-    (a counter file holds one row per counter per dispatch)."""
+    """Rows of the dispatches after the second-to-last multiply-accumulate launch up to the last one, or
+    between the last two marks (a counter file holds one row per counter per dispatch)."""
     key = "Dispatch_Id" if "Dispatch_Id" in rows[0] else "Start_Timestamp"
-    mac = sorted({int(r[key]) for r in rows if MAC in r["Kernel_Name"]})
-    if len(mac) < 2:
-        raise SystemExit("need at least two multiply-accumulate launches (a warm-up and a timed step)")
-    return [r for r in rows if mac[-2] < int(r[key]) <= mac[-1]]
+    end = sorted({int(r[key]) for r in rows if (MARK or MAC) in r["Kernel_Name"]})
+    if len(end) < 2:
+        raise SystemExit("need at least two marks" if MARK else
+                         "need at least two multiply-accumulate launches (a warm-up and a timed step)")
+    return [r for r in rows if end[-2] < int(r[key]) <= end[-1] and not (MARK and MARK in r["Kernel_Name"])]
 
 
 def _calib(rows, counter):
@@ -125,7 +132,8 @@ def trace(trace_csv):
         a[0] += 1
         a[1] += (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3
     span = (int(rows[-1]["End_Timestamp"]) - t0) / 1e3
-    out = [f"Span of one level (first dispatch to the multiply-accumulate's end): {span:.1f} us; kernels "
+    what = "one pass" if MARK else "one level (first dispatch to the multiply-accumulate's end)"
+    out = [f"Span of {what}: {span:.1f} us; kernels "
            "on two streams overlap, so their durations sum to more than the span.", "",
            "| kernel | launches | total us | avg us |", "|---|---:|---:|---:|"]
     for k, (cnt, us) in sorted(agg.items(), key=lambda kv: -kv[1][1]):
@@ -170,6 +178,9 @@ def waves(*csvs):
 
 
 if __name__ == "__main__":
+    if len(sys.argv) > 3 and sys.argv[-2] == "--mark":
+        MARK = sys.argv[-1]
+        del sys.argv[-2:]
     if len(sys.argv) == 4 and sys.argv[1] == "traffic":
         print(traffic(sys.argv[2], sys.argv[3]))
     elif len(sys.argv) == 3 and sys.argv[1] == "trace":

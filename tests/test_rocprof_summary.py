@@ -68,6 +68,16 @@ def test_trace_lists_the_level_span(tmp_path):
     assert "k_warm" not in txt
 
 
+def test_marks_delimit_a_pass(tmp_path, monkeypatch):
+    monkeypatch.setattr(rs, "MARK", "sin_kernel")
+    rows = [("k_warm", 64, 0.0), ("sin_kernel_cuda", 64, 0.0), ("k_tensor", 64, 0.0), ("k_mac_diag3<32>", 64, 0.0),
+            ("k_mac_diag3<32>", 64, 0.0), ("k_ntt_inv_b", 64, 0.0), ("sin_kernel_cuda", 64, 0.0)]
+    _write(tmp_path / "t.csv", "none", rows)
+    txt = rs.trace(str(tmp_path / "t.csv"))
+    assert "| k_tensor | 1 |" in txt and "| k_mac_diag3 | 2 |" in txt and "| k_ntt_inv_b | 1 |" in txt
+    assert "k_warm" not in txt and "sin_kernel" not in txt
+
+
 def test_waves_normalises_by_wave_cycles_over_the_level(tmp_path):
     # two counters per dispatch, as rocprofv3 writes them: one row per counter
     path = tmp_path / "sq.csv"
